@@ -19,10 +19,8 @@ constexpr int kSplitBuffers = 2;
 constexpr int split_buffers_deep(int group) { return group <= 2 ? 5 : group == 4 ? 3 : 2; }
 constexpr int kDeepMinPages = 4 * kSplitWaves;   // shard pages (at full capacity) for deep buffers
 
-// Dispatch orders of the sweep's units (see decode_split.hip).
-constexpr int kOrderByRequest = 0;
-constexpr int kOrderByShardDesc = 1;
-// Shards at least this long (pages, at full capacity) are swept in kOrderByShardDesc.
+// Shards at least this long (pages, at full capacity) are swept in the long-shard order (largest
+// shard first), shorter ones in the short-shard order (dealt to the XCDs by items; decode_split.hip).
 constexpr int kLongShardPages = 128;
 // Relative page shares of the sub-shard chunks of a long shard that run on even- and odd-numbered
 // XCDs (decode_split.hip): the odd XCDs stream slower.
@@ -47,9 +45,11 @@ struct SplitParams {
   float* out_lse;               // fp32 [B, max_shards, chunks, Hq]
   int32_t batch, hq, hkv, max_pages, num_pages, max_shards, chunks;
   int32_t n_units;              // B * max_shards * chunks * Hkv
-  int32_t units_per_xcd;        // ceil(n_units / 8)
-  int32_t order;                // kOrderByRequest or kOrderByShardDesc (dispatch order of units)
-  // kOrderByShardDesc with chunks == 1 only, or null: [8 * units_per_xcd] int32 that an ordering
+  // Short-shard order: units of an item, which run on one XCD (hkv, or 1 where that would leave
+  // the XCDs uneven); long-shard order: 0.
+  int32_t run;
+  int32_t units_per_xcd;        // workgroup indices per XCD: whole items (run > 0), ceil(n_units / 8)
+  // The long-shard order with chunks == 1 only, or null: [8 * units_per_xcd] int32 that an ordering
   // kernel, launched just before the sweep, fills with the unit each workgroup index sweeps (-1:
   // none): longest shard first, dealt to the XCDs by kXcdWeightEven / kXcdWeightOdd
   // (rank_shift: log2 of the length buckets' width in pages).

@@ -80,16 +80,23 @@ int64_t choose_chunks(const qf_decode_desc* d) {
 }
 
 // Long shards: long-lived workgroups, the dispatch order decides the tail (largest first).
-// Short shards: short workgroups, prologue latency decides (keep a request on one XCD).
-int sweep_order(const qf_decode_desc* d, int64_t chunks) {
+// Short shards: short workgroups, spread evenly over the XCDs.
+bool long_shards(const qf_decode_desc* d, int64_t chunks) {
   const int64_t shard_pages = (d->max_pages_per_seq + d->max_shards - 1) / d->max_shards / chunks;
-  return shard_pages >= qf::kLongShardPages ? qf::kOrderByShardDesc : qf::kOrderByRequest;
+  return shard_pages >= qf::kLongShardPages;
+}
+
+// Units of one item of the short-shard order (decode_split.hip): the KV heads of a (request, shard,
+// chunk) stay on one XCD, unless so few items would leave an XCD over an eighth more work than the
+// mean; then every unit is an item of its own.
+int32_t units_per_item(const qf_decode_desc* d, int64_t items) {
+  return (items + 7) / 8 * 64 <= items * 9 ? d->n_kv_heads : 1;
 }
 
 // An unchunked long-shard sweep (of up to kRankMaxPairs (request, shard) pairs) takes its units in
 // the order of rank_units_kernel, which it keeps in the workspace: one int32 per workgroup index.
 bool ranks_units(const qf_decode_desc* d, int64_t chunks) {
-  return chunks == 1 && sweep_order(d, chunks) == qf::kOrderByShardDesc &&
+  return chunks == 1 && long_shards(d, chunks) &&
          (int64_t)d->batch * d->max_shards <= qf::kRankMaxPairs;
 }
 size_t unit_order_bytes(const qf_decode_desc* d, int64_t chunks) {
@@ -180,9 +187,11 @@ int prepare_split(const qf_decode_desc* desc, const void* q, const void* k_cache
   p.max_shards = d.max_shards;
   p.chunks = (int32_t)chunks;
   p.n_units = (int32_t)units;
-  p.units_per_xcd = (int32_t)((units + 7) / 8);
+  const bool long_order = long_shards(&d, chunks);
+  const int64_t items = (int64_t)d.batch * d.max_shards * chunks;
+  p.run = long_order ? 0 : units_per_item(&d, items);
+  p.units_per_xcd = (int32_t)(p.run > 0 ? (units / p.run + 7) / 8 * p.run : (units + 7) / 8);
   const int64_t shard_pages = (d.max_pages_per_seq + d.max_shards - 1) / d.max_shards / chunks;
-  p.order = sweep_order(&d, chunks);
   p.unit_order = rank ? reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + state_bytes)
                       : nullptr;
   p.rank_shift = 0;
@@ -190,7 +199,7 @@ int prepare_split(const qf_decode_desc* desc, const void* q, const void* k_cache
   // Deep buffers cost occupancy (two wavefronts per SIMD instead of three), so a chunked sweep,
   // whose chunk count fills exactly the resident workgroups of the two-buffer kernel, keeps two
   // buffers (deep ones would leave a second, partial round: -2% on the 131,072-position share).
-  p.deep = p.order == qf::kOrderByRequest && shard_pages >= qf::kDeepMinPages && chunks == 1;
+  p.deep = !long_order && shard_pages >= qf::kDeepMinPages && chunks == 1;
   p.scale_log2 = (float)((double)d.softmax_scale * 1.4426950408889634);
 
   sp->group = d.n_q_heads / d.n_kv_heads;
