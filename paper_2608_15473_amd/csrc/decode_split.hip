@@ -26,7 +26,7 @@
 
 #include <atomic>
 
-#include "linear_body.h"
+#include "linear_mfma.h"
 #include "merge_body.h"
 #include "qf_internal.h"
 
@@ -931,7 +931,8 @@ sweep_beside_linear_kernel(
     const uint16_t* __restrict__ w,
     const uint16_t* __restrict__ gain, const uint16_t* __restrict__ residual,
     uint16_t* __restrict__ out_a, uint16_t* __restrict__ out_b, int32_t M, int32_t N, int32_t K,
-    int32_t n_split, float eps, int32_t prologue, int32_t glu, int32_t linear_groups) {
+    int32_t n_split, float eps, int32_t prologue, int32_t glu, int32_t tiles,
+    int32_t linear_groups) {
   static_assert(64 * kSplitWaves == lin::kThreads, "both roles use the same workgroup size");
   const unsigned j = blockIdx.x / 8u, lane8 = blockIdx.x % 8u;
   const unsigned long long S = (unsigned)units_per_xcd, T = S + (unsigned)linear_groups;
@@ -946,6 +947,29 @@ sweep_beside_linear_kernel(
   }
   constexpr int U = 2, R = lin::beside_rows(MB), RG = lin::beside_rows_glu(MB);
   const unsigned lb = 8u * (j - before) + lane8;
+  if constexpr (MB > lin::kVectorRows) {
+    if (tiles) {
+      constexpr int RW = lin::kTileRows;
+      __shared__ lin::TileLds<1, kSplitWaves> lds;
+      const int n0 = (int)lb * RW;
+      if (prologue == kProRmsNorm) {
+        if (glu)
+          lin::linear_tiles<kProRmsNorm, 1, kSplitWaves, 1, true>(
+              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, lds);
+        else
+          lin::linear_tiles<kProRmsNorm, 1, kSplitWaves, 1, false>(
+              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, lds);
+      } else {
+        if (glu)
+          lin::linear_tiles<kProNone, 1, kSplitWaves, 1, true>(
+              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, lds);
+        else
+          lin::linear_tiles<kProNone, 1, kSplitWaves, 1, false>(
+              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, lds);
+      }
+      return;
+    }
+  }
   if (glu) {
     if (prologue == kProRmsNorm)
       lin::linear_rows<kProRmsNorm, MB, U, RG, true>(x, w, gain, residual, out_a, out_b, M, N, K,
@@ -968,8 +992,10 @@ sweep_beside_linear_kernel(
 
 template <int G, int MB>
 hipError_t launch_beside(const SplitParams& p, const LinearParams& l, hipStream_t stream) {
+  const bool tiles = lin::takes_tiles(l);
   const int rows = l.glu ? lin::beside_rows_glu(MB) : lin::beside_rows(MB);
-  const int linear_groups = (lin::linear_blocks(l.N, rows) + 7) / 8;
+  const int linear_groups = ((tiles ? (l.N + lin::kTileRows - 1) / lin::kTileRows
+                                    : lin::linear_blocks(l.N, rows)) + 7) / 8;
   const unsigned grid = 8u * ((unsigned)p.units_per_xcd + (unsigned)linear_groups);
   const hipError_t e = launch_rank(p, stream);
   if (e != hipSuccess) return e;
@@ -979,7 +1005,7 @@ hipError_t launch_beside(const SplitParams& p, const LinearParams& l, hipStream_
                      p.n_units, p.units_per_xcd, p.batch, p.run, p.scale_log2, p.unit_order,
                      l.x, l.w, l.gain,
                      l.residual, l.out_a, l.out_b, l.M, l.N, l.K, l.n_split, l.eps, l.prologue,
-                     l.glu ? 1 : 0, linear_groups);
+                     l.glu ? 1 : 0, tiles ? 1 : 0, linear_groups);
   return hipGetLastError();
 }
 

@@ -6,7 +6,8 @@
 // The paper names N1, N2 only as normalisations and M as a feed-forward; the RMS form and the
 // SwiGLU feed-forward are those of the Qwen3 blocks it converts.
 //
-// At decode a block sees a handful of rows (M <= 8), so each product is a weight stream: the
+// At decode a block sees a handful of rows (M <= 8), so each product is a weight stream.  This is
+// the vector path, which one input row and the SwiGLU prologue take (more rows: linear_mfma.h): the
 // kernel reads W once (N x K bf16, 16-byte loads), and the few input rows come from L1/L2.  One
 // wavefront computes one output row n for every input row: its lanes stride K by 8 elements, each
 // holding an fp32 partial per input row, reduced across the wavefront at the end.  The prologue is

@@ -1,0 +1,101 @@
+"""The matrix-core products (2 to 8 input rows) at the edges of their tiles: K around a block (64), a
+round (1,024) and the rounds in flight, N that is odd, below a workgroup's share, and at every
+number of tiles per workgroup (1 to 5, and two workgroups per compute unit), through qf_linear and
+beside a sweep (another decomposition: bitwise the same).
+
+Gate: the bf16 values around the exact result widened by the fp32 accumulation bound of the other
+product tests, (K/64 + 32) 2^-24 of the absolute sum.  Infinities and NaN in x, the gains and the
+weights: the outputs that are not finite are those of the vector path (one row at a time), and alike."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2608_15473_amd as qf
+from parity import bf16_neighbours, say
+from workloads import make_case
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # (M, N, K, prologue, residual, split, GLU output)
+    (2, 1, 8, None, False, None, False),
+    (8, 2, 64, "rms_norm", False, None, True),
+    (3, 7, 72, None, True, 3, False),
+    (5, 250, 1016, "rms_norm", True, None, False),
+    (8, 513, 1024, None, True, 512, False),
+    (4, 2050, 1032, "rms_norm", False, None, True),       # 2 tiles, a short second round
+    (7, 4602, 2048, "rms_norm", False, 4096, False),      # 3 tiles
+    (8, 6400, 3080, None, False, None, True),
+    (6, 8001, 1096, "rms_norm", True, None, False),       # 4 tiles
+    (2, 10240, 136, None, True, None, False),             # 5 tiles
+    (8, 10242, 2120, "rms_norm", False, None, True),      # two workgroups per compute unit: 3 tiles
+    (3, 14400, 200, None, False, 7, False),               # 4 tiles
+    (8, 20000, 1992, "rms_norm", False, None, False),     # 5 tiles
+    (8, 264, 9736, None, True, None, False),              # 10 rounds
+    (5, 1026, 5128, "rms_norm", False, None, True),
+]
+
+
+def _inputs(gpu, M, N, K, pro, res):
+    gen = torch.Generator(device=gpu).manual_seed(M * 131 + N * 17 + K)
+    x = torch.randn(M, K, generator=gen, device=gpu).to(torch.bfloat16)
+    x *= torch.tensor([1.0, 1e-3, 30.0, 1.0, 3.0, 0.5, 1.0, 2.0], device=gpu)[:M, None]
+    w = (torch.randn(N, K, generator=gen, device=gpu) / K ** 0.5).to(torch.bfloat16)
+    g = (torch.rand(K, generator=gen, device=gpu) + 0.5).to(torch.bfloat16) if pro else None
+    r = torch.randn(M, N, generator=gen, device=gpu).to(torch.bfloat16) if res else None
+    return x, w, g, r
+
+
+@pytest.mark.parametrize("M,N,K,pro,res,split,glu", CASES)
+def test_tiles_match_the_oracle_and_the_shared_launch(gpu, M, N, K, pro, res, split, glu):
+    x, w, g, r = _inputs(gpu, M, N, K, pro, res)
+    kw = dict(prologue=pro, gain=g, eps=1e-6, residual=r, split=split, glu_out=glu)
+    say(f"[tiles] M={M} N={N} K={K} {pro} residual={res} split={split} glu={glu}")
+    got = qf.linear(x, w, **kw)
+    case = make_case(2, 4, 2, [300, 17], [2, 1], seed=3, device=gpu)
+    beside = qf.attn_decode_split_beside(case.q, case.k_cache, case.v_cache, case.block_table,
+                                         case.ctx_lens, case.n_shards, dict(x=x, w=w, **kw),
+                                         max_shards=2, scale=case.scale)[2]
+    torch.cuda.synchronize()
+    got, beside = (torch.cat(t, 1) if split is not None and split < N else t for t in (got, beside))
+    assert torch.equal(got.view(torch.int16), beside.view(torch.int16))
+    xd, wd = x.double().cpu().numpy(), w.double().cpu().numpy()
+    px = oracle.rms_norm(xd, g.double().cpu().numpy(), 1e-6) if pro else xd
+    ref, bound = px @ wd.T, np.abs(px) @ np.abs(wd).T
+    eps = (K / 64 + 32) * 2.0 ** -24
+    if glu:
+        gate, up = ref[:, 0::2], ref[:, 1::2]
+        ref = oracle.swiglu(gate, up)
+        delta = (1.1 * np.abs(up) * eps * bound[:, 0::2]
+                 + np.abs(oracle.silu(gate)) * eps * bound[:, 1::2] + 1e-6 * np.abs(ref))
+    else:
+        rd = r.double().cpu().numpy() if res else 0.0
+        ref = ref + rd
+        delta = eps * (bound + np.abs(rd))
+    lo, _ = bf16_neighbours(ref - delta)
+    _, hi = bf16_neighbours(ref + delta)
+    out = got.double().cpu().numpy()
+    ok = (out >= lo) & (out <= hi)
+    assert ok.all(), (np.argwhere(~ok)[:4], out[~ok][:4], ref[~ok][:4])
+
+
+@pytest.mark.parametrize("pro", [None, "rms_norm"])
+def test_non_finite_inputs_come_out_as_on_the_vector_path(gpu, pro):
+    M, N, K = 6, 40, 1160
+    x, w, g, _ = _inputs(gpu, M, N, K, pro, False)
+    inf, nan = float("inf"), float("nan")
+    x[1, 5], x[2, 1100], x[3, 7] = inf, -inf, nan
+    w[3, 9], w[4, 1159], w[5, 0] = inf, -inf, nan
+    x[0, 9] = 1.0                     # a factor of few bits against an infinite weight
+    w[6, 5] = 0.0                     # 0 times an infinite input
+    if g is not None:
+        g[700] = inf
+        g[701:] = 1.0
+    got = qf.linear(x, w, pro, g, 1e-6).float()
+    one = torch.cat([qf.linear(x[m:m + 1], w, pro, g, 1e-6) for m in range(M)]).float()
+    torch.cuda.synchronize()
+    same = torch.isfinite(one)
+    assert torch.equal(torch.isnan(got), torch.isnan(one))
+    assert torch.equal(got[~same & ~torch.isnan(one)], one[~same & ~torch.isnan(one)])
+    torch.testing.assert_close(got[same], one[same], rtol=2 ** -7, atol=1e-4)
