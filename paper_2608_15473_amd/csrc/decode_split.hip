@@ -78,6 +78,19 @@ __device__ __forceinline__ float group_bcast(float x, int h) {
   }
 }
 
+// Rows (16 lanes) or halves (32 lanes) of two registers exchanged: x = (a's even, b's even),
+// y = (a's odd, b's odd), in lane order.
+__device__ __forceinline__ void swap_rows(float a, float b, float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_halves(float a, float b, float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
+}
+
 // 16-byte slot of chunk `ch` (dims 8ch..8ch+7) of position `pos` in a wavefront's 4 KB K tile in
 // LDS.  The XOR swizzle makes both the row-wise writes and the column-wise operand reads free of
 // bank conflicts: a position's 16 chunks stay in its 256 bytes, and the 16 positions read together
@@ -242,15 +255,14 @@ __device__ __forceinline__ void sweep_unit(
     float* __restrict__ merged_lse = nullptr, const int32_t* __restrict__ unit_order = nullptr) {
   // Which unit this workgroup sweeps.  Workgroups are dispatched in index order, round-robin over
   // the 8 XCDs.
-  //  * Short shards (run > 0): items of `run` units (run = hkv: every KV head of one
-  //    (request, shard, chunk), so an item's query, context length and block-table lines meet in
-  //    one XCD's L2; run = 1 where there are too few items for that) are dealt to the XCDs in rows
-  //    of 8 consecutive items, each row rotated against the one before, so that the shards of one
-  //    request, and the first shards of all requests, spread over every XCD whatever the shard
+  //  * Short shards (run > 0): items of `run` units (the KV heads of some consecutive (shard, chunk)
+  //    slots of a request, in (request, shard, chunk, KV head) order) are dealt to the XCDs in rows
+  //    of 8 consecutive items, each row rotated against the one before, so that the slots of one
+  //    request, and the first slots of all requests, spread over every XCD whatever the shard
   //    counts: in a ragged batch a few long requests hold most of the pages, and with each XCD
   //    taking a contiguous range of units those requests' sweeps ran on one or two XCDs.  Measured:
-  //    12 requests of 27 to 7,003 positions at 16 shards, sweep + fold 41.4 -> 29.6 us a layer; 4
-  //    requests of up to 5,987 in the one-launch decode 23.2 -> 20.2 us; uniform batches +-0.5%.
+  //    12 requests of 27 to 7,003 positions at 16 shards, sweep + fold 37 -> 28 us a layer; 14 of up to
+  //    25,056 at 35 shards 109 -> 65 us; uniform batches +-0.5%.
   //  * Long shards (run == 0): units in (shard descending, request, KV head) order,
   //    round-robin over the XCDs, so the largest shards (high indices exist only in long requests)
   //    start first and every XCD gets an even share; the small shards fill the tail.  With
@@ -295,6 +307,36 @@ __device__ __forceinline__ void sweep_unit(
     s = max_shards - 1 - rest / batch;
   }
 
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row = lane >> 4;
+  const int col = lane & 15;
+
+  // With 4 or 8 heads per KV head the scores come from the matrix cores (process_mf below);
+  // otherwise the VALU computes them (process_valu).  Measured: the matrix path is 1-5% faster at
+  // G = 4 and 27-32% faster at G = 8, where the VALU path spends most of its issue slots on the
+  // dot products and reductions, and 1-2.5% slower at G = 2, where the VALU has slack and the LDS
+  // round trip only adds latency.
+  constexpr bool MF = G >= 4;
+
+  // Queries of the group, requested ahead of everything that waits for the request's shape.  VALU path: dims 8col..8col+7 of every head as packed bf16 pairs.
+  // Matrix path: the queries are the 16 columns of the B operand of S^T = K Q^T (column c holds
+  // head c % G), split over the dims in 4 steps of 32: lane (row, col) holds dims
+  // 32kk + 8row .. 32kk + 8row + 7 of head col % G for step kk.
+  uint32_t qv[G][4];
+  bf16x8_t qb[4];
+  if constexpr (MF) {
+    const uint4* qrow = reinterpret_cast<const uint4*>(qp + ((size_t)b * hq + (size_t)g * G + col % G) * D);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) qb[kk] = __builtin_bit_cast(bf16x8_t, qrow[4 * kk + row]);
+  } else {
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const uint4 t = reinterpret_cast<const uint4*>(qp + ((size_t)b * hq + (size_t)g * G + h) * D)[col];
+      qv[h][0] = t.x; qv[h][1] = t.y; qv[h][2] = t.z; qv[h][3] = t.w;
+    }
+  }
+
   // The request's shape, checked: an out-of-range value poisons this unit's log-sum-exp with NaN.
   const ShardRange range = shard_range(ctx_lens, n_shards, b, s, max_pages, max_shards);
   const int n = range.n;
@@ -337,36 +379,6 @@ __device__ __forceinline__ void sweep_unit(
     return;
   }
 
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int row = lane >> 4;
-  const int col = lane & 15;
-
-  // With 4 or 8 heads per KV head the scores come from the matrix cores (process_mf below);
-  // otherwise the VALU computes them (process_valu).  Measured: the matrix path is 1-5% faster at
-  // G = 4 and 27-32% faster at G = 8, where the VALU path spends most of its issue slots on the
-  // dot products and reductions, and 1-2.5% slower at G = 2, where the VALU has slack and the LDS
-  // round trip only adds latency.
-  constexpr bool MF = G >= 4;
-
-  // Queries of the group.  VALU path: dims 8col..8col+7 of every head as packed bf16 pairs.
-  // Matrix path: the queries are the 16 columns of the B operand of S^T = K Q^T (column c holds
-  // head c % G), split over the dims in 4 steps of 32: lane (row, col) holds dims
-  // 32kk + 8row .. 32kk + 8row + 7 of head col % G for step kk.
-  uint32_t qv[G][4];
-  bf16x8_t qb[4];
-  if constexpr (MF) {
-    const uint4* qrow = reinterpret_cast<const uint4*>(qp + ((size_t)b * hq + (size_t)g * G + col % G) * D);
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) qb[kk] = __builtin_bit_cast(bf16x8_t, qrow[4 * kk + row]);
-  } else {
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const uint4 t = reinterpret_cast<const uint4*>(qp + ((size_t)b * hq + (size_t)g * G + h) * D)[col];
-      qv[h][0] = t.x; qv[h][1] = t.y; qv[h][2] = t.z; qv[h][3] = t.w;
-    }
-  }
-
   // Online-softmax state.  VALU path: every lane keeps (m, l) of all G heads for its row.  Matrix
   // path: lane (row, col) keeps them for head col % G only (m1, l1); the other heads' values sit
   // in the same quad (8-lane group at G = 8) and are broadcast when needed.  acc: dims 8col..8col+7 of every head.
@@ -389,28 +401,25 @@ __device__ __forceinline__ void sweep_unit(
   // This wavefront's pages: c0 + wave + i * W for i < mine.
   const int mine = (c1 - c0 > wave) ? (c1 - c0 - wave + W - 1) / W : 0;
   auto page_of = [&](int i) { return c0 + wave + i * W; };
-  // Raw block-table entry of page i (read one page past the last one in flight; checked only when
-  // used, so the scalar load's latency hides behind the pages in flight).
+  // Raw block-table entry of page i, checked only when used; past either end, that of the page there
+  // (so that the entries of a group of buffers are read without a test, in one go).
   auto entry = [&](int i) -> int {
-    if (i >= mine) return 0;
-    const int pg = page_of(i);
+    const int pg = page_of(min(max(i, 0), mine - 1));
     return bt ? bt[pg] : b * max_pages + pg;
   };
   // One 4 KB page of one KV head through a buffer resource whose size covers the page's cached
-  // positions only: loads past it return zeros, so a page that does not exist (size 0) costs no
-  // traffic and keeps the prefetch below unconditional and the wait counts static, and the slots
+  // positions only: loads past it return zeros, so the slots
   // past the last position of a partial page read as zeros instead of whatever the pool holds
   // there (a zero V meets a zero weight; the scores of those slots are set to -inf).  The loads
   // are non-temporal (cache policy nt): every cached byte is read exactly once per sweep, and on
   // gfx950 streaming reads marked nt reach a markedly higher share of HBM bandwidth than
   // default-policy reads.
   auto issue = [&](uint4* kk, uint4* vv, int ph, int i) {
-    const bool live = i < mine;
     if ((unsigned)ph >= (unsigned)num_pages) {
-      poison |= live;
+      poison = true;
       ph = 0;
     }
-    const int bytes = live ? min(n - page_of(i) * P, P) * D * 2 : 0;
+    const int bytes = min(n - page_of(i) * P, P) * D * 2;
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t*>(kbase + (size_t)ph * page_stride), (short)0, bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
@@ -539,32 +548,57 @@ __device__ __forceinline__ void sweep_unit(
     accumulate(vc, [&](int j, int h) { return pr[j][h]; });
   };
 
-  // Rotation over NBUF register buffers: pages i+1 .. i+NBUF-1 stream in while page i is
-  // computed.  Scalar loads may return out of order, so waiting for one waits for all: each
-  // block-table entry is requested only after the previous one has been consumed by issue().
+  // Rotation over NBUF register buffers, all of them in flight while the oldest is waited for: page
+  // i is computed, then page i + NBUF requested into its buffer.  No load is issued for a page that does
+  // not exist: it would move no data but still take the compute unit's address path 16 cycles a load,
+  // 8 loads a page, which a unit of a few pages per wavefront cannot hide.  So the wavefront's pages
+  // are preceded by `pad` slots without a page, which only the first group and the computing skip (by
+  // uniform branches): the loop's loads are unconditional and its wait counts exact.
+  // Block-table entries come a group at a time: scalar loads may return out of order, so waiting for
+  // one waits for all, and a group is requested once the one before has been used.
   uint4 kbuf[NBUF][4], vbuf[NBUF][4];
+  if (mine > 0) {
+    const int pad = (NBUF - mine % NBUF) % NBUF;
+    int ent[NBUF];
 #pragma unroll
-  for (int t = 0; t < NBUF - 1; ++t) issue(kbuf[t], vbuf[t], entry(t), t);
-  // The query loads (issued first) must have landed before the loop, so that the only loads in
-  // flight inside it are the page buffers; the first pages stay in flight meanwhile
-  // (s_waitcnt vmcnt(8 * (NBUF - 1)), expcnt 7, lgkmcnt 15).
-  constexpr int kAhead = 8 * (NBUF - 1);
-  __builtin_amdgcn_s_waitcnt((kAhead & 0xF) | ((kAhead >> 4) << 14) | 0x0F70);
-  int ph_next = entry(NBUF - 1);
-  for (int i = 0; i < mine; i += NBUF) {
-#pragma unroll
-    for (int t = 0; t < NBUF; ++t) {
-      const int ahead = i + t + NBUF - 1;
-      issue(kbuf[(t + NBUF - 1) % NBUF], vbuf[(t + NBUF - 1) % NBUF], ph_next, ahead);
-      ph_next = entry(ahead + 1);
-      if (i + t >= mine) goto swept;
+    for (int t = 0; t < NBUF; ++t) ent[t] = entry(t - pad);
+    auto process = [&](int t, int i) {
       if constexpr (MF)
-        process_mf(kbuf[t], vbuf[t], page_of(i + t));
+        process_mf(kbuf[t], vbuf[t], page_of(i));
       else
-        process_valu(kbuf[t], vbuf[t], page_of(i + t));
-    }
+        process_valu(kbuf[t], vbuf[t], page_of(i));
+    };
+#pragma unroll
+    for (int t = 0; t < NBUF; ++t)
+      if (t == NBUF - 1 || t >= pad) issue(kbuf[t], vbuf[t], ent[t], t - pad);
+    int next = NBUF - pad;   // the first page not requested yet; the buffers hold next - NBUF + t
+#pragma unroll
+    for (int t = 0; t < NBUF; ++t) ent[t] = entry(next + t);
+    auto group = [&](bool first) {
+      int now[NBUF];
+#pragma unroll
+      for (int t = 0; t < NBUF; ++t) {
+        if (!first || next - NBUF + t >= 0) process(t, next - NBUF + t);
+        if (t == 0) {
+#pragma unroll
+          for (int u = 0; u < NBUF; ++u) now[u] = ent[u];
+        }
+        issue(kbuf[t], vbuf[t], now[t], next + t);
+        if (t == 0) {
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < NBUF; ++u) ent[u] = entry(next + NBUF + u);
+        }
+      }
+      next += NBUF;
+    };
+    // The first group apart where there are more than two buffers: its waits must hold for any pad.
+    if (NBUF > 2 && next < mine) group(true);
+    while (next < mine) group(NBUF <= 2);
+#pragma unroll
+    for (int t = 0; t < NBUF; ++t)
+      if (t == NBUF - 1 || next - NBUF + t >= 0) process(t, next - NBUF + t);
   }
-swept:
   if constexpr (MF) {
 #pragma unroll
     for (int h = 0; h < G; ++h) {
@@ -573,36 +607,41 @@ swept:
     }
   }
 
-  // Merge the 4 rows of the wavefront (lanes col, col+16, col+32, col+48 hold the same dims).
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    float M = fmaxf(m[h], __shfl_xor(m[h], 16));
-    M = fmaxf(M, __shfl_xor(M, 32));
-    const float f = (M == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m[h] - M);
-    float lh = l[h] * f;
-    lh += __shfl_xor(lh, 16);
-    lh += __shfl_xor(lh, 32);
-    l[h] = lh;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float a = acc[h][e] * f;
-      a += __shfl_xor(a, 16);
-      a += __shfl_xor(a, 32);
-      acc[h][e] = a;
-    }
-    m[h] = M;
-  }
-
-  // Merge the W wavefronts through LDS and write the unit's (O, ln Z).
+  // Merge the 4 rows of the wavefront (lanes col, col+16, col+32, col+48 hold the same dims), by
+  // swapping registers between rows: the sums of 8 dims take 4 row swaps and 2 half swaps, and leave
+  // each row with 2 of them (rows 0..3: dims 0-1, 4-5, 2-3, 6-7), each (r0 + r1) + (r2 + r3).
   __shared__ float s_acc[W][G][D];
   __shared__ float s_m[W][G];
   __shared__ float s_l[W][G];
   __shared__ int s_bad[W];
-  if (row == 0) {
 #pragma unroll
-    for (int h = 0; h < G; ++h)
+  for (int h = 0; h < G; ++h) {
+    float M = m[h], x, y;
+    swap_rows(M, M, x, y);
+    M = fmaxf(x, y);
+    swap_halves(M, M, x, y);
+    M = fmaxf(x, y);
+    const float f = (M == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m[h] - M);
+    float lh = l[h] * f;
+    swap_rows(lh, lh, x, y);
+    lh = x + y;
+    swap_halves(lh, lh, x, y);
+    l[h] = x + y;
+    m[h] = M;
+    float c[4], d[2];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s_acc[wave][h][col * 8 + e] = acc[h][e];
+    for (int e = 0; e < 4; ++e) {
+      swap_rows(acc[h][e] * f, acc[h][e + 4] * f, x, y);
+      c[e] = x + y;
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      swap_halves(c[e], c[e + 2], x, y);
+      d[e] = x + y;
+    }
+    // Merge the W wavefronts through LDS and write the unit's (O, ln Z).
+    *reinterpret_cast<float2*>(&s_acc[wave][h][col * 8 + (row & 1) * 4 + (row & 2)]) =
+        make_float2(d[0], d[1]);
   }
   // Any poisoned wavefront poisons the unit: a ballot per wavefront, met in LDS at the barrier
   // the merge needs anyway (cheaper in registers than __syncthreads_or, which rebuilds a flat
@@ -1019,6 +1058,12 @@ hipError_t launch_beside_g(const SplitParams& p, const LinearParams& l, hipStrea
   }
 }
 
+// Workgroups of the two-buffer kernel that the chunk rule counts as resident per compute unit: those of
+// the kernel's earlier register counts, which the rule was measured with (per-GPU share of a 2^20
+// request, 1,024 instead of 768 at G = 2: 90.4 -> 91.3 us, more workgroups in flight only add
+// contention), never more than the device holds.
+constexpr int counted_per_unit(int group) { return group == 1 ? 4 : group == 8 ? 2 : 3; }
+
 template <int G>
 int resident_g() {
   int dev = 0, cus = 0, per_cu = 0;
@@ -1030,7 +1075,7 @@ int resident_g() {
     (void)hipGetLastError();  // leave no error behind for the next launch check
     return 0;
   }
-  return cus * per_cu;
+  return cus * (per_cu < counted_per_unit(G) ? per_cu : counted_per_unit(G));
 }
 
 }  // namespace

@@ -45,8 +45,7 @@ struct SplitParams {
   float* out_lse;               // fp32 [B, max_shards, chunks, Hq]
   int32_t batch, hq, hkv, max_pages, num_pages, max_shards, chunks;
   int32_t n_units;              // B * max_shards * chunks * Hkv
-  // Short-shard order: units of an item, which run on one XCD (hkv, or 1 where that would leave
-  // the XCDs uneven); long-shard order: 0.
+  // Short-shard order: units of an item, which run on one XCD; long-shard order: 0.
   int32_t run;
   int32_t units_per_xcd;        // workgroup indices per XCD: whole items (run > 0), ceil(n_units / 8)
   // The long-shard order with chunks == 1 only, or null: [8 * units_per_xcd] int32 that an ordering

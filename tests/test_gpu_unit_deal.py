@@ -35,3 +35,20 @@ def test_every_unit_is_swept_once(gpu, batch, shards, hkv, G):
     np.testing.assert_allclose(lse.cpu().numpy(), got["lse"], rtol=1e-6, atol=1e-6)
     if qf.split_chunks(qf.make_desc(case.q, case.k_cache, case.block_table, shards, case.scale)) == 1:
         assert np.array_equal(out.view(torch.int16).cpu().numpy(), got["out_bits"])
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("max_pages", [48, 128])   # the deep short-shard buffers, the long-shard ones
+def test_every_number_of_pages_per_wavefront(gpu, G, max_pages):
+    """One shard per request of 1 to 48 pages (0 to 12 per wavefront), whole and partial: the page
+    buffers' first group, loop and end at every remainder.  Sampled heads, at the parity gates."""
+    pages = np.arange(1, 49)
+    ctx = 16 * pages - (pages * 7) % 16
+    hkv = 24                                           # enough units for unchunked shards
+    case = make_case(48, G * hkv, hkv, ctx, 1, seed=950 + G, max_pages=max_pages, device=gpu)
+    desc = qf.make_desc(case.q, case.k_cache, case.block_table, 1, case.scale)
+    assert qf.split_chunks(desc) == 1
+    say(f"[deal] 1 to 48 pages, G {G}, capacity {max_pages}")
+    pairs = [(b, (b * 5 + i * (G * hkv // 4 + 1)) % (G * hkv)) for b in range(48) for i in range(4)]
+    got = run_gpu(case)
+    check(case, got, oracle_ref(case, pairs), pairs, label="pages")
