@@ -13,7 +13,7 @@
  * partition, any order; an empty shard is ln Z = -inf with a vector that is never read).
  *
  * Entry points: the sweep and its merge (qf_attn_decode_split, qf_attn_combine, or both in one
- * launch: qf_attn_decode, and qf_attn_decode_noalloc for callers that cannot allocate;
+ * launch: qf_attn_decode; and qf_attn_decode_noalloc for callers that cannot allocate;
  * qf_attn_decode_split_unfolded leaves sub-shard chunks as extra slots); the decode step
  * around them (qf_attn_combine_current folds in the current token, qf_kv_append writes it to the
  * cache, qf_attn_combine_current_append does both in one launch); the dense products of a decoder block (qf_linear) and the sweep sharing one launch with
@@ -196,11 +196,10 @@ int qf_attn_decode(const qf_decode_desc* desc, const void* q, const void* k_cach
 /*
  * qf_attn_decode for callers that cannot allocate device memory or pass a workspace (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same sweep and
- * merge in one launch, with the same results (bitwise) as qf_attn_decode on the same inputs, but
- * the partial states and the per-(request, KV head) counters live in a fixed device array of the
- * library's own, QF_NOALLOC_SCRATCH_BYTES (64 MiB) on every GPU the library runs on, held until the
- * process ends.  The call allocates nothing; it enqueues a small kernel that clears the counters
- * it will use, then the decode.
+ * merge, with the same results (bitwise) as qf_attn_decode on the same inputs, but the partial
+ * states live in a fixed device array of the library's own, QF_NOALLOC_SCRATCH_BYTES (64 MiB) on every
+ * GPU the library runs on, held until the process ends.  The call allocates nothing; it enqueues
+ * two kernels, the sweep and the merge (there are no arrival counters to keep).
  *
  *   q ... n_shards, out, lse   as for qf_attn_decode.
  *   stream                     hipStream_t of the CURRENT device (the scratch used is the current

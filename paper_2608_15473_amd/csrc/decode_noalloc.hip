@@ -1,12 +1,17 @@
-// Fixed device scratch for the allocation-free one-launch decode (qf_attn_decode_noalloc).
+// Fixed device scratch for the allocation-free decode (qf_attn_decode_noalloc).
 //
-// The one-launch decode keeps the partial states of every (shard, chunk) slot and one arrival
-// counter per (request, KV head) in device memory beyond its inputs and outputs.  For callers that
-// cannot allocate (graph capture, serving loops, harnesses that forbid hipMalloc) that memory is
-// this file-scope array: every GPU the library runs on holds its own copy for the life of the
-// process.  Host code never passes the array's name to a kernel (on the host it is only a stand-in
-// for the symbol); the device address of each GPU's copy is looked up once per device with
-// hipGetSymbolAddress and kept, and only that address is used.
+// The decode keeps the partial states of every (shard, chunk) slot in device memory beyond its inputs
+// and outputs.  For callers that cannot allocate (graph capture, serving loops, harnesses that forbid
+// hipMalloc) that memory is this file-scope array: every GPU the library runs on holds its own copy
+// for the life of the process.  Host code never passes the array's name to a kernel (on the host it is
+// only a stand-in for the symbol); the device address of each GPU's copy is looked up once per device
+// with hipGetSymbolAddress and kept, and only that address is used.
+//
+// The decode here is the sweep's launch and the merge's.  One launch whose last workgroup of a
+// (request, KV head) merges needs arrival counters, which this array cannot be trusted to hold at zero
+// (calls may have raced on it), so a kernel cleared them first: two launches as well, of which the
+// fused one waits for every workgroup's stores and counts them.  Measured in a HIP graph, 4 ragged
+// requests of up to 5,987 positions at G = 4: 19.6 -> 17.2 us a layer.
 #include <atomic>
 #include <mutex>
 
@@ -27,17 +32,9 @@ constexpr int kMaxDevices = 64;
 std::atomic<unsigned char*> g_scratch[kMaxDevices];
 std::mutex g_setup;
 
-__global__ void __launch_bounds__(256) zero_i32(int32_t* __restrict__ p, int32_t n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
 }  // namespace
 
-hipError_t noalloc_prepare(int32_t n_counters, hipStream_t stream, int32_t** counters,
-                           void** states) {
-  if (n_counters < 0 || (size_t)n_counters * sizeof(int32_t) > kNoallocCounterBytes)
-    return hipErrorInvalidValue;
+hipError_t noalloc_states(void** states) {
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
@@ -56,17 +53,7 @@ hipError_t noalloc_prepare(int32_t n_counters, hipStream_t stream, int32_t** cou
       g_scratch[dev].store(base, std::memory_order_release);
     }
   }
-  *counters = reinterpret_cast<int32_t*>(base);
   *states = base + kNoallocCounterBytes;
-  // The counters must start at zero.  The decode leaves the entries it used at zero, but the
-  // array keeps whatever the last call on this GPU left, so they are cleared on every call, with
-  // a kernel (no memset node if the caller captures the call into a graph).
-  if (n_counters > 0) {
-    hipLaunchKernelGGL(zero_i32, dim3((n_counters + 255) / 256), dim3(256), 0, stream, *counters,
-                       n_counters);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   return hipSuccess;
 }
 

@@ -75,11 +75,11 @@ hipError_t launch_w(const MergeParams& p, bool to_bf16, unsigned grid, hipStream
 // and 8 instead of 16 for 96 slots the per-GPU share of the 2^20-token request's 0.5%.  The result
 // does not depend on W as long as one round suffices: every wavefront sums the same 16 slots, and
 // the wavefronts without slots add exact zeros in the cross-wavefront merge.
-hipError_t launch_merge(const MergeParams& p, bool to_bf16, hipStream_t stream) {
+hipError_t launch_merge(const MergeParams& p, bool to_bf16, hipStream_t stream, int max_waves) {
   const unsigned grid = (unsigned)p.rows * (unsigned)p.hq;
   if (grid == 0) return hipSuccess;
-  if (p.entries > 128) return launch_w<16>(p, to_bf16, grid, stream);
-  if (p.entries > 64) return launch_w<8>(p, to_bf16, grid, stream);
+  if (p.entries > 128 && max_waves >= 16) return launch_w<16>(p, to_bf16, grid, stream);
+  if (p.entries > 64 && max_waves >= 8) return launch_w<8>(p, to_bf16, grid, stream);
   if (p.entries > 32) return launch_w<4>(p, to_bf16, grid, stream);
   if (p.entries > 16) return launch_w<2>(p, to_bf16, grid, stream);
   return launch_w<1>(p, to_bf16, grid, stream);

@@ -127,14 +127,13 @@ int simulate_schedule(int R, const double* arrival, const double* attn_time, int
 hipError_t launch_decode_split(const SplitParams& p, int group, hipStream_t stream);
 
 // The allocation-free decode's fixed scratch (decode_noalloc.hip): one device array per GPU of
-// kNoallocScratchBytes, the counters in its first kNoallocCounterBytes, the partial states after.
+// kNoallocScratchBytes, the partial states after its first kNoallocCounterBytes (unused; they and the
+// bound on (request, KV head) groups that they stood for are part of the interface).
 constexpr size_t kNoallocScratchBytes = size_t(64) << 20;
 constexpr size_t kNoallocCounterBytes = size_t(256) << 10;
 constexpr size_t kNoallocStateBytes = kNoallocScratchBytes - kNoallocCounterBytes;
-// This device's scratch (looked up on the first call on the device): *counters (n_counters int32
-// entries, cleared to zero on `stream` before anything else is enqueued there) and *states.
-hipError_t noalloc_prepare(int32_t n_counters, hipStream_t stream, int32_t** counters,
-                           void** states);
+// This device's scratch (looked up on the first call on the device).
+hipError_t noalloc_states(void** states);
 
 // Workgroups of the long-shard sweep (kSplitBuffers) at group size `group` that are resident on
 // the current device at once (compute units x workgroups per unit); 0 when there is no device to
@@ -142,6 +141,8 @@ hipError_t noalloc_prepare(int32_t n_counters, hipStream_t stream, int32_t** cou
 int split_resident_workgroups(int group);
 // to_bf16 = false: partial-state output (fp32 O not written for an empty row);
 // to_bf16 = true:  final output (bf16, +0 for an empty row).
-hipError_t launch_merge(const MergeParams& p, bool to_bf16, hipStream_t stream);
+// max_waves: at most this many wavefronts per row (a row of more slots than one round of them covers
+// takes more rounds; the sums of a row depend on it only then).
+hipError_t launch_merge(const MergeParams& p, bool to_bf16, hipStream_t stream, int max_waves = 16);
 
 }  // namespace qf

@@ -400,9 +400,9 @@ int qf_attn_decode_noalloc(const qf_decode_desc* desc, const void* q, const void
 
 namespace {
 
-// fixed_scratch: workspace and counters are the library's own scratch array (decode_noalloc.hip),
-// looked up and its counters cleared only once every argument has passed its checks, so that a
-// refused call enqueues nothing.
+// fixed_scratch: the partial states are in the library's own scratch array (decode_noalloc.hip), looked
+// up only once every argument has passed its checks, and the sweep and the merge are two launches (with
+// the fused merge's 4 wavefronts per row, so that the sums are the same).
 int decode_fused(const qf_decode_desc* desc, const void* q, const void* k_cache,
                  const void* v_cache, const int32_t* block_table, const int32_t* ctx_lens,
                  const int32_t* n_shards, void* out, float* lse, void* workspace,
@@ -427,7 +427,7 @@ int decode_fused(const qf_decode_desc* desc, const void* q, const void* k_cache,
     // Placeholders (aligned, never dereferenced) until the arguments have been checked.
     workspace = reinterpret_cast<void*>(uintptr_t(256));
     workspace_size = need;
-    counters = reinterpret_cast<int32_t*>(uintptr_t(256));
+    counters = reinterpret_cast<int32_t*>(uintptr_t(256));  // not used
     n_counters = groups;
     if (!out) return fail(QF_EINVAL, "out is required");
   } else if (!out || !workspace || !counters) {
@@ -453,11 +453,24 @@ int decode_fused(const qf_decode_desc* desc, const void* q, const void* k_cache,
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (fixed_scratch) {
     void* base = nullptr;
-    const hipError_t e = qf::noalloc_prepare((int32_t)groups, s, &counters, &base);
+    hipError_t e = qf::noalloc_states(&base);
     if (e != hipSuccess) return fail(QF_EHIP, "scratch set-up: %s", hipGetErrorString(e));
     states = static_cast<float*>(base);
     sp.p.out_o = states;
     sp.p.out_lse = states + n_states * qf::kHeadDim;
+    e = qf::launch_decode_split(sp.p, sp.group, s);
+    if (e != hipSuccess) return fail(QF_EHIP, "decode launch: %s", hipGetErrorString(e));
+    qf::MergeParams m{};
+    m.in_o = sp.p.out_o;
+    m.in_lse = sp.p.out_lse;
+    m.out_o = out;
+    m.out_lse = lse;
+    m.rows = d.batch;
+    m.entries = (int32_t)(d.max_shards * chunks);
+    m.hq = d.n_q_heads;
+    e = qf::launch_merge(m, true, s, qf::kSplitWaves);
+    if (e != hipSuccess) return fail(QF_EHIP, "merge launch: %s", hipGetErrorString(e));
+    return QF_OK;
   }
   const hipError_t e = qf::launch_decode_fused(sp.p, sp.group, counters, out, lse, s);
   if (e != hipSuccess) return fail(QF_EHIP, "decode launch: %s", hipGetErrorString(e));
