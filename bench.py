@@ -343,9 +343,9 @@ def stage_kernel_times(stack, u, w, shape, passes=2):
     partials = B * S * Hq * (D + 1) * 4
     sweep = B * n * Hkv * D * 4 + B * (-(-n // 16)) * 4 + B * Hq * D * 2 + partials
     nbytes = {
-        "W_q": lin(Hq * D, H),
-        "sweep + W_gate,W_up": sweep + lin(2 * I, H) - B * I * 2,    # writes the activation
-        "W_down": lin(H, I, gain=False, res=True),
+        # one read of u for both; the second writes the activation
+        "W_q + W_gate,W_up": lin(Hq * D, H) + lin(2 * I, H) - B * H * 2 - B * I * 2,
+        "sweep + W_down": sweep + lin(H, I, gain=False, res=True),
         "W_k,W_v": lin(2 * Hkv * D, H),
         # partials, q, k_j and v_j read; out and lse written; k_j and v_j written to the cache and
         # ctx_lens read and advanced

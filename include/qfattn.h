@@ -16,7 +16,8 @@
  * launch: qf_attn_decode; and qf_attn_decode_noalloc for callers that cannot allocate;
  * qf_attn_decode_split_unfolded leaves sub-shard chunks as extra slots); the decode step
  * around them (qf_attn_combine_current folds in the current token, qf_kv_append writes it to the
- * cache, qf_attn_combine_current_append does both in one launch); the dense products of a decoder block (qf_linear) and the sweep sharing one launch with
+ * cache, qf_attn_combine_current_append does both in one launch); the dense products of a decoder block
+ * (qf_linear, qf_linear_pair) and the sweep sharing one launch with
  * one of them (qf_attn_decode_split_beside); and a host-side simulation of the layer-wise decode
  * schedule (qf_schedule_simulate).
  *
@@ -47,7 +48,7 @@
 extern "C" {
 #endif
 
-#define QF_VERSION 8
+#define QF_VERSION 9
 
 #define QF_OK 0
 #define QF_EINVAL (-1)       /* null pointer, negative or inconsistent size, Hq % Hkv != 0   */
@@ -362,7 +363,7 @@ int qf_linear(int32_t rows, int32_t n_out, int32_t k, int32_t prologue, const vo
               const void* w, const void* gain, float eps, const void* residual, void* out,
               int32_t n_split, void* out_b, void* stream);
 
-/* The arguments of one qf_linear call, as a struct (for qf_attn_decode_split_beside). */
+/* The arguments of one qf_linear call, as a struct (for the calls that issue it with another). */
 typedef struct {
   int32_t rows, n_out, k, prologue;
   const void* x;
@@ -374,6 +375,16 @@ typedef struct {
   int32_t n_split;
   void* out_b;
 } qf_linear_args;
+
+/*
+ * Exactly qf_linear(*first) and qf_linear(*second), in one launch where the two can share one: the same
+ * rows and k, both behind RMS prologues, the second with a GLU output (W_q N1(u) and W_gate|W_up N2(u)
+ * of a block, which read the same u); otherwise as two launches.  Bitwise the two calls.  Neither
+ * call's outputs may overlap the other's inputs or outputs.  Both are checked before anything is
+ * launched; the structs are HOST pointers, read during the call.  With rows == 0 in one of them only the
+ * other is issued.  Returns the codes of qf_linear.
+ */
+int qf_linear_pair(const qf_linear_args* first, const qf_linear_args* second, void* stream);
 
 /*
  * The sweep beside the feed-forward (§3: the sweep of one layer and the feed-forward of another

@@ -39,5 +39,6 @@ from .binding import (  # noqa: F401
     schedule_simulate,
     make_desc,
     linear,
+    linear_pair,
     workspace_size,
 )

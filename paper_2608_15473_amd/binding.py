@@ -20,7 +20,7 @@ EXPORTED = ("qf_attn_decode_split_workspace_size", "qf_attn_decode_split", "qf_a
             "qf_attn_decode_split_chunks", "qf_attn_decode_split_unfolded",
             "qf_attn_decode_workspace_size", "qf_attn_decode", "qf_attn_decode_noalloc",
             "qf_attn_combine_current", "qf_attn_combine_current_append", "qf_kv_append",
-            "qf_linear", "qf_attn_decode_split_beside",
+            "qf_linear", "qf_linear_pair", "qf_attn_decode_split_beside",
             "qf_schedule_simulate", "qf_last_error", "qf_version")
 QF_WIRING_QFIRST, QF_WIRING_COMPOSED = 0, 1
 QF_LINEAR_PLAIN, QF_LINEAR_RMS_NORM, QF_LINEAR_SWIGLU, QF_LINEAR_GLU_OUT = 0, 1, 2, 16
@@ -81,6 +81,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.qf_kv_append.argtypes = [ctypes.POINTER(DecodeDesc), vp, vp, vp, vp, vp, vp, i32, vp, vp]
     lib.qf_linear.argtypes = [i32, i32, i32, i32, vp, vp, vp, ctypes.c_float, vp, vp, i32, vp,
                               vp]
+    lib.qf_linear_pair.argtypes = [ctypes.POINTER(LinearArgs), ctypes.POINTER(LinearArgs), vp]
     lib.qf_attn_decode_split_beside.argtypes = [ctypes.POINTER(DecodeDesc), vp, vp, vp, vp, vp, vp,
                                                 vp, vp, vp, sz, ctypes.POINTER(LinearArgs), vp]
     dp = ctypes.POINTER(ctypes.c_double)
@@ -94,7 +95,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                  "qf_attn_decode_workspace_size", "qf_attn_decode", "qf_attn_decode_noalloc",
                  "qf_attn_combine", "qf_attn_combine_current", "qf_attn_combine_current_append",
                  "qf_kv_append",
-                 "qf_linear", "qf_attn_decode_split_beside", "qf_schedule_simulate", "qf_version"):
+                 "qf_linear", "qf_linear_pair", "qf_attn_decode_split_beside",
+                 "qf_schedule_simulate", "qf_version"):
         getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     return lib
@@ -481,6 +483,16 @@ def linear(x, w, prologue=None, gain=None, eps=1e-6, residual=None, out=None, sp
                                     la.eps, la.residual, la.out, la.n_split, la.out_b,
                                     ctypes.c_void_p(stream)))
     return result
+
+
+def linear_pair(first, second):
+    """Two products in one launch where they can share one (qf_linear_pair): ``first`` and ``second``
+    are dicts of ``linear``'s keyword arguments; returns both outputs, bitwise those of two calls."""
+    a, out_a = _linear_call(**first)
+    b, out_b = _linear_call(**second)
+    stream = torch.cuda.current_stream(first["x"].device).cuda_stream
+    _check(load_library().qf_linear_pair(ctypes.byref(a), ctypes.byref(b), ctypes.c_void_p(stream)))
+    return out_a, out_b
 
 
 def decode_workspace_size(desc: DecodeDesc) -> int:

@@ -32,12 +32,23 @@ void launch_tiles(const LinearParams& p, int rows, hipStream_t stream) {
                      p.N, p.K, p.n_split, p.eps, rows);
 }
 
+// The output rows of a workgroup (even) for products of n and m outputs in one launch, and the
+// workgroups per compute unit that makes: as few as keep a workgroup within 40 rows (5 tiles), all of
+// them of one size.
+struct TileShare {
+  int per_unit, rows;
+};
+TileShare tile_share(int64_t n, int64_t m) {
+  constexpr int64_t kUnits = 256, kMost = 40;
+  const int64_t per_unit = (n + m + kUnits * kMost - 1) / (kUnits * kMost);
+  int64_t rows = ((n + m + kUnits * per_unit - 1) / (kUnits * per_unit) + 1) / 2 * 2;
+  while (rows < kMost && (n + rows - 1) / rows + (m + rows - 1) / rows > kUnits * per_unit) rows += 2;
+  return {(int)per_unit, (int)rows};
+}
+
 template <int PRO, bool GLU>
 void launch_tiles_pro(const LinearParams& p, hipStream_t stream) {
-  // Workgroups per compute unit: as few as keep a workgroup within 40 rows (5 tiles).
-  constexpr int kUnits = 256, kMost = 40;
-  const int per_unit = (p.N + kUnits * kMost - 1) / (kUnits * kMost);
-  const int rows = ((p.N + kUnits * per_unit - 1) / (kUnits * per_unit) + 1) / 2 * 2;
+  const auto [per_unit, rows] = tile_share(p.N, 0);
   const int t = (rows + lin::kTileRows - 1) / lin::kTileRows;
   // Rounds in flight: as many as 128 registers hold (the RMS prologue also keeps the gains and the
   // halves).
@@ -81,9 +92,54 @@ void launch_pro(const LinearParams& p, hipStream_t stream) {
   switch (lin::pick_unroll(p.M, p.K)) {
     case 1: launch_u<PRO, MB, 1>(p, stream); break;
     case 2: launch_u<PRO, MB, (cap >= 2 ? 2 : 1)>(p, stream); break;
+    case 3: launch_u<PRO, MB, (cap >= 3 ? 3 : 1)>(p, stream); break;
     case 4: launch_u<PRO, MB, (cap >= 4 ? 4 : 1)>(p, stream); break;
+    case 5: launch_u<PRO, MB, (cap >= 5 ? 5 : 1)>(p, stream); break;
+    case 6: launch_u<PRO, MB, (cap >= 6 ? 6 : 1)>(p, stream); break;
+    case 7: launch_u<PRO, MB, (cap >= 7 ? 7 : 1)>(p, stream); break;
     default: launch_u<PRO, MB, (cap >= 8 ? 8 : 1)>(p, stream); break;
   }
+}
+
+// Two products of the same input rows in one launch: the workgroups of the first, then those of the
+// second, each doing what it would in its own launch.
+template <int U>
+__global__ void __launch_bounds__(lin::kThreads)
+linear_pair_kernel(const LinearParams a, const LinearParams b, int32_t blocks_a) {
+  if ((int)blockIdx.x < blocks_a)
+    lin::linear_rows<kProRmsNorm, 1, U, 1, false>(a.x, a.w, a.gain, a.residual, a.out_a, a.out_b, a.M,
+                                                  a.N, a.K, a.n_split, a.eps, blockIdx.x);
+  else
+    lin::linear_rows<kProRmsNorm, 1, U, 2, true>(b.x, b.w, b.gain, b.residual, b.out_a, b.out_b, b.M,
+                                                 b.N, b.K, b.n_split, b.eps, blockIdx.x - blocks_a);
+}
+
+template <int T, int W, int RB>
+__global__ void __launch_bounds__(64 * W)
+linear_pair_tiles_kernel(const LinearParams a, const LinearParams b, int32_t blocks_a, int32_t rows) {
+  __shared__ lin::TileLds<T, W> lds;
+  if ((int)blockIdx.x < blocks_a)
+    lin::linear_tiles<kProRmsNorm, T, W, RB, false>(a.x, a.w, a.gain, a.residual, a.out_a, a.out_b,
+                                                    a.M, a.N, a.K, a.n_split, a.eps,
+                                                    (int)blockIdx.x * rows, rows, lds);
+  else
+    lin::linear_tiles<kProRmsNorm, T, W, RB, true>(b.x, b.w, b.gain, b.residual, b.out_a, b.out_b, b.M,
+                                                   b.N, b.K, b.n_split, b.eps,
+                                                   ((int)blockIdx.x - blocks_a) * rows, rows, lds);
+}
+
+template <int U>
+void launch_pair_u(const LinearParams& a, const LinearParams& b, hipStream_t stream) {
+  const int blocks_a = lin::linear_blocks(a.N, 1);
+  hipLaunchKernelGGL((linear_pair_kernel<U>), dim3(blocks_a + lin::linear_blocks(b.N, 2)),
+                     dim3(lin::kThreads), 0, stream, a, b, blocks_a);
+}
+
+template <int T, int W, int RB>
+void launch_pair_tiles(const LinearParams& a, const LinearParams& b, int rows, hipStream_t stream) {
+  const int blocks_a = (a.N + rows - 1) / rows;
+  hipLaunchKernelGGL((linear_pair_tiles_kernel<T, W, RB>), dim3(blocks_a + (b.N + rows - 1) / rows),
+                     dim3(64 * W), 0, stream, a, b, blocks_a, rows);
 }
 
 template <int PRO>
@@ -113,6 +169,50 @@ hipError_t launch_linear(const LinearParams& p, hipStream_t stream) {
     launch_rows<kProSwiglu>(p, stream);
   else
     launch_rows<kProNone>(p, stream);
+  return hipGetLastError();
+}
+
+// A projection and the gated product of the same rows behind RMS prologues (W_q and W_gate|W_up of a
+// block) share a launch; any other two products are launched one after the other.
+hipError_t launch_linear_pair(const LinearParams& a, const LinearParams& b, hipStream_t stream) {
+  const bool pair = a.M > 0 && a.M == b.M && a.K == b.K && a.prologue == kProRmsNorm &&
+                    b.prologue == kProRmsNorm && !a.glu && b.glu &&
+                    lin::takes_tiles(a) == lin::takes_tiles(b) && (a.M == 1 || lin::takes_tiles(a)) &&
+                    (int64_t)a.N + b.N <= INT32_MAX / 2;
+  if (!pair) {
+    const hipError_t e = launch_linear(a, stream);
+    return e != hipSuccess ? e : launch_linear(b, stream);
+  }
+  if (!lin::takes_tiles(a)) {
+    switch (lin::pick_unroll(1, a.K)) {
+      case 1: launch_pair_u<1>(a, b, stream); break;
+      case 2: launch_pair_u<2>(a, b, stream); break;
+      case 3: launch_pair_u<3>(a, b, stream); break;
+      case 4: launch_pair_u<4>(a, b, stream); break;
+      case 5: launch_pair_u<5>(a, b, stream); break;
+      case 6: launch_pair_u<6>(a, b, stream); break;
+      case 7: launch_pair_u<7>(a, b, stream); break;
+      default: launch_pair_u<8>(a, b, stream); break;
+    }
+    return hipGetLastError();
+  }
+  const auto [per_unit, rows] = tile_share(a.N, b.N);
+  const int t = (rows + lin::kTileRows - 1) / lin::kTileRows;
+  if (per_unit == 1) {
+    switch (t) {
+      case 1: launch_pair_tiles<1, 16, 3>(a, b, rows, stream); break;
+      case 2: launch_pair_tiles<2, 16, 2>(a, b, rows, stream); break;
+      case 3: launch_pair_tiles<3, 16, 2>(a, b, rows, stream); break;
+      case 4: launch_pair_tiles<4, 16, 1>(a, b, rows, stream); break;
+      default: launch_pair_tiles<5, 16, 1>(a, b, rows, stream); break;
+    }
+  } else {
+    switch (t) {
+      case 3: launch_pair_tiles<3, 8, 1>(a, b, rows, stream); break;
+      case 4: launch_pair_tiles<4, 8, 1>(a, b, rows, stream); break;
+      default: launch_pair_tiles<5, 8, 1>(a, b, rows, stream); break;
+    }
+  }
   return hipGetLastError();
 }
 

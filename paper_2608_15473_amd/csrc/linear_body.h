@@ -204,14 +204,22 @@ inline int linear_blocks(int N, int R) { return (N + kRowsPerBlock * R - 1) / (k
 constexpr int beside_rows(int MB) { return MB <= 2 ? 4 : MB <= 4 ? 2 : 1; }
 constexpr int beside_rows_glu(int MB) { return MB <= 2 ? 4 : 2; }
 
-// U for a row length K: enough chunks to cover K in one group where registers allow (at most 8
-// loads of weights plus 8 of inputs per lane).
+// U for a row length K: the chunks of K in one group where registers allow (at most 8 loads of weights
+// plus 8 of inputs per lane), else the group size in 4 .. 8 that leaves the fewest chunks past the end
+// (a load past the end moves nothing but takes the address path as long as any other).
 inline int pick_unroll(int M, int K) {
   const int cap = (M <= 1) ? 8 : (M <= 2) ? 4 : (M <= 4) ? 2 : 1;
   const int need = (K / 8 + 63) / 64;
-  int u = 1;
-  while (u < cap && u < need) u *= 2;
-  return u;
+  if (cap < 8) {
+    int u = 1;
+    while (u < cap && u < need) u *= 2;
+    return u;
+  }
+  if (need <= cap) return need;
+  int best = cap;
+  for (int u = cap - 1; u >= 4; --u)
+    if ((need + u - 1) / u * u < (need + best - 1) / best * best) best = u;
+  return best;
 }
 
 inline int rows_bucket(int M) { return (M <= 1) ? 1 : (M <= 2) ? 2 : (M <= 4) ? 4 : 8; }

@@ -109,6 +109,7 @@ struct LinearParams {
   bool glu;                  // rows of W alternate gate / up; out = silu(gate) * up, N / 2 columns
 };
 hipError_t launch_linear(const LinearParams& p, hipStream_t stream);
+hipError_t launch_linear_pair(const LinearParams& a, const LinearParams& b, hipStream_t stream);
 // The sweep with the merge fused into its last workgroup per (request, KV head)
 // (decode_split.hip): p.out_o / p.out_lse hold the partial states, counters [batch * hkv] int32
 // start at zero and are left at zero.

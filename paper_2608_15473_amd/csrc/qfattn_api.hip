@@ -651,6 +651,24 @@ int qf_linear(int32_t rows, int32_t n_out, int32_t k, int32_t prologue, const vo
   return QF_OK;
 }
 
+int qf_linear_pair(const qf_linear_args* first, const qf_linear_args* second, void* stream) {
+  g_error[0] = 0;
+  if (!first || !second) return fail(QF_EINVAL, "first and second are required");
+  qf::LinearParams a{}, b{};
+  bool noop_a = false, noop_b = false;
+  int rc = prepare_linear(first, &a, &noop_a);
+  if (rc) return rc;
+  rc = prepare_linear(second, &b, &noop_b);
+  if (rc) return rc;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (noop_a && noop_b) return QF_OK;
+  const hipError_t e = noop_a   ? qf::launch_linear(b, s)
+                       : noop_b ? qf::launch_linear(a, s)
+                                : qf::launch_linear_pair(a, b, s);
+  if (e != hipSuccess) return fail(QF_EHIP, "linear_pair launch: %s", hipGetErrorString(e));
+  return QF_OK;
+}
+
 int qf_attn_decode_split_beside(const qf_decode_desc* desc, const void* q, const void* k_cache,
                                 const void* v_cache, const int32_t* block_table,
                                 const int32_t* ctx_lens, const int32_t* n_shards,

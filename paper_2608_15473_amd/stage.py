@@ -14,8 +14,11 @@ the two may run at once.  On one GPU this module offers three orders of the same
                                         |                              + append -> z + W_o attn = y
     attention stream:                   +--> sweep of the layer's cache (split into shards) --^
 
-  mode="fused":    the sweep and W_gate|W_up N2(u) in one launch whose workgroups take either
-                   role (qf_attn_decode_split_beside), so the two share every CU.
+  mode="fused":    W_q N1(u) and W_gate|W_up N2(u), which read the same u, in one launch
+                   (qf_linear_pair), then the sweep and u + W_down(.), neither of which waits for the
+                   other, in one launch whose workgroups take either role
+                   (qf_attn_decode_split_beside), so the two share every CU: five launches a block
+                   instead of seven.
 
 Every step is one of the library's HIP kernels: the four products fused with the normalisation
 or activation that feeds them and the residual add that follows (qf_linear), the sweep, and the merge
@@ -131,21 +134,27 @@ class QFirstStack:
         w, c = self.layers[l], self.caches[l]
         B = self.B
         main = torch.cuda.current_stream(self.device)
-        with self._span("W_q"):                                             # q reads u
-            self._linear(u, w["w_q"], self.q.view(B, -1), "rms_norm", w["g1"])
-        if mode == "fused":                                                  # sweep | W_gate|W_up
+        if mode == "fused":
+            with self._span("W_q + W_gate,W_up"):                            # both read u
+                for r in range(0, B, 8):
+                    e = min(B, r + 8)
+                    qf.linear_pair(
+                        dict(x=u[r:e], w=w["w_q"], prologue="rms_norm", gain=w["g1"], eps=self.eps,
+                             out=self.q[r:e].view(e - r, -1)),
+                        dict(x=u[r:e], w=w["w_gu"], prologue="rms_norm", gain=w["g2"],
+                             eps=self.eps, out=self.act[r:e], glu_out=True))
             head = min(B, 8)
-            with self._span("sweep + W_gate,W_up"):
+            with self._span("sweep + W_down"):                               # z = u + M(N2 u)
                 qf.attn_decode_split_beside(
                     self.q, c.k_cache, c.v_cache, c.block_table, c.ctx_lens, c.n_shards,
-                    dict(x=u[:head], w=w["w_gu"], prologue="rms_norm", gain=w["g2"], eps=self.eps,
-                         out=self.act[:head], glu_out=True),
+                    dict(x=self.act[:head], w=w["w_down"], residual=u[:head], out=self.z[:head]),
                     max_shards=self.max_shards, scale=self.scale, part_out=self.part_out,
                     part_lse=self.part_lse, workspace=self.workspace)
                 if B > head:
-                    self._linear(u[head:], w["w_gu"], self.act[head:], "rms_norm", w["g2"],
-                                 glu_out=True)
+                    self._linear(self.act[head:], w["w_down"], self.z[head:], residual=u[head:])
         else:
+            with self._span("W_q"):                                          # q reads u
+                self._linear(u, w["w_q"], self.q.view(B, -1), "rms_norm", w["g1"])
             if mode == "streams":
                 self.attn_stream.wait_stream(main)
                 with torch.cuda.stream(self.attn_stream), self._span("sweep"):
@@ -155,8 +164,8 @@ class QFirstStack:
                     self._sweep(c)
             with self._span("W_gate,W_up"):                                  # the feed-forward
                 self._linear(u, w["w_gu"], self.act, "rms_norm", w["g2"], glu_out=True)
-        with self._span("W_down"):                                           # z = u + M(N2 u)
-            self._linear(self.act, w["w_down"], self.z, residual=u)
+            with self._span("W_down"):                                       # z = u + M(N2 u)
+                self._linear(self.act, w["w_down"], self.z, residual=u)
         with self._span("W_k,W_v"):                                          # k, v read z
             self._linear(self.z, w["w_kv"], self.k.view(B, -1), "rms_norm", w["g1"],
                          out_b=self.v.view(B, -1))

@@ -99,3 +99,25 @@ def test_non_finite_inputs_come_out_as_on_the_vector_path(gpu, pro):
     assert torch.equal(torch.isnan(got), torch.isnan(one))
     assert torch.equal(got[~same & ~torch.isnan(one)], one[~same & ~torch.isnan(one)])
     torch.testing.assert_close(got[same], one[same], rtol=2 ** -7, atol=1e-4)
+
+
+@pytest.mark.parametrize("M,N,I,K", [(1, 2048, 3072, 1024), (1, 33, 5, 2568), (1, 8, 40, 9736),
+                                     (2, 250, 7, 1032), (8, 2048, 3072, 1024), (5, 4095, 6000, 72),
+                                     (8, 4096, 9728, 328), (3, 5000, 1, 64)])
+def test_pair_equals_the_two_calls_bitwise(gpu, M, N, I, K):
+    """A projection and a gated product of the same rows in one launch: every share of rows per
+    workgroup, both paths (one row, several), every group of chunks of a row's K."""
+    x, wa, ga, _ = _inputs(gpu, M, N, K, "rms_norm", False)
+    _, wb, gb, _ = _inputs(gpu, M, 2 * I, K, "rms_norm", False)
+    a = dict(x=x, w=wa, prologue="rms_norm", gain=ga, split=(N + 1) // 2)
+    b = dict(x=x, w=wb, prologue="rms_norm", gain=gb, glu_out=True)
+    say(f"[tiles] pair M={M} N={N} I={I} K={K}")
+    (p1, p2), q = qf.linear_pair(a, b)
+    (r1, r2), s = qf.linear(**a), qf.linear(**b)
+    torch.cuda.synchronize()
+    for got, ref in ((p1, r1), (p2, r2), (q, s)):
+        assert torch.equal(got.view(torch.int16), ref.view(torch.int16))
+    # two products that cannot share a launch
+    y, z = qf.linear_pair(b, dict(x=x, w=wa))
+    assert torch.equal(y.view(torch.int16), s.view(torch.int16))
+    assert torch.equal(z.view(torch.int16), qf.linear(x, wa).view(torch.int16))
