@@ -352,6 +352,10 @@ def stage_kernel_times(stack, u, w, shape, passes=2):
         "merge, current-token fold + cache append": partials + B * Hq * D * 2
         + 2 * B * Hkv * D * 2 + B * Hq * (D * 2 + 4) + 2 * B * Hkv * D * 2 + 8 * B,
         "W_o": lin(H, Hq * D, gain=False, res=True),
+        # one request: the merged fp32 pair between the two
+        "W_k,W_v + merge": lin(2 * Hkv * D, H) + partials + B * Hq * (D + 1) * 4,
+        "current-token fold + cache append + W_o": lin(H, Hq * D, gain=False, res=True)
+        + B * Hq * (D + 1) * 4 + B * Hq * D * 2 + 4 * B * Hkv * D * 2 + B * Hq * 4 + 8 * B,
     }
     out = {}
     for name, ev in spans.items():

@@ -48,7 +48,7 @@
 extern "C" {
 #endif
 
-#define QF_VERSION 9
+#define QF_VERSION 10
 
 #define QF_OK 0
 #define QF_EINVAL (-1)       /* null pointer, negative or inconsistent size, Hq % Hkv != 0   */
@@ -385,6 +385,41 @@ typedef struct {
  * other is issued.  Returns the codes of qf_linear.
  */
 int qf_linear_pair(const qf_linear_args* first, const qf_linear_args* second, void* stream);
+
+/*
+ * qf_linear(*product) and the merge of shard slots (qf_attn_combine's, with the merged pairs left in fp32
+ * for qf_linear_attn_current), in one launch for one request and one row behind the RMS prologue
+ * (W_k|W_v N1(z) of a block needs nothing of the sweep), otherwise as two.
+ *
+ *   product     HOST pointer; its outputs must not overlap the merge's inputs or outputs, or the reverse.
+ *   batch ... part_lse   as for qf_attn_combine.
+ *   merged_out  fp32 [B, Hq, D], 16-byte aligned; not written where every slot is empty.
+ *   merged_lse  fp32 [B, Hq] natural log; -inf where every slot is empty.
+ */
+int qf_linear_beside_merge(const qf_linear_args* product, int32_t batch, int32_t n_q_heads,
+                           int32_t head_dim, int32_t max_shards, const float* part_out,
+                           const float* part_lse, float* merged_out, float* merged_lse,
+                           void* stream);
+
+/*
+ * The end of a block's attention for ONE request in one launch: the current token folded into the merged
+ * pair of its cache (qf_attn_combine_current's fold), the fold's attention and log-sum-exp written, the
+ * token appended to the cache (qf_kv_append with advance = 1), and qf_linear(*product) of the attention
+ * (W_o, with its residual).
+ *
+ *   desc        batch (0: nothing is done; more than 1: QF_EUNSUPPORTED), heads, cache shape and scale.
+ *   merged_out, merged_lse   as written by qf_linear_beside_merge (merged_out 16-byte aligned).
+ *   q, k_cur, v_cur   as for qf_attn_combine_current, 16-byte aligned.
+ *   attn        bf16 [1, Hq, D], 16-byte aligned; lse fp32 [1, Hq] or NULL.
+ *   k_cache ... status   as for qf_kv_append.
+ *   product     HOST pointer: rows == batch, k == Hq * D, QF_LINEAR_PLAIN, x == attn; its outputs must
+ *               not overlap any other argument.
+ */
+int qf_linear_attn_current(const qf_decode_desc* desc, const float* merged_out,
+                           const float* merged_lse, const void* q, const void* k_cur,
+                           const void* v_cur, void* attn, float* lse, void* k_cache, void* v_cache,
+                           const int32_t* block_table, int32_t* ctx_lens, int32_t* status,
+                           const qf_linear_args* product, void* stream);
 
 /*
  * The sweep beside the feed-forward (§3: the sweep of one layer and the feed-forward of another

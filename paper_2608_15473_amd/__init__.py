@@ -39,6 +39,8 @@ from .binding import (  # noqa: F401
     schedule_simulate,
     make_desc,
     linear,
+    linear_attn_current,
+    linear_beside_merge,
     linear_pair,
     workspace_size,
 )

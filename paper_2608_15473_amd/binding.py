@@ -20,8 +20,8 @@ EXPORTED = ("qf_attn_decode_split_workspace_size", "qf_attn_decode_split", "qf_a
             "qf_attn_decode_split_chunks", "qf_attn_decode_split_unfolded",
             "qf_attn_decode_workspace_size", "qf_attn_decode", "qf_attn_decode_noalloc",
             "qf_attn_combine_current", "qf_attn_combine_current_append", "qf_kv_append",
-            "qf_linear", "qf_linear_pair", "qf_attn_decode_split_beside",
-            "qf_schedule_simulate", "qf_last_error", "qf_version")
+            "qf_linear", "qf_linear_pair", "qf_linear_beside_merge", "qf_linear_attn_current",
+            "qf_attn_decode_split_beside", "qf_schedule_simulate", "qf_last_error", "qf_version")
 QF_WIRING_QFIRST, QF_WIRING_COMPOSED = 0, 1
 QF_LINEAR_PLAIN, QF_LINEAR_RMS_NORM, QF_LINEAR_SWIGLU, QF_LINEAR_GLU_OUT = 0, 1, 2, 16
 
@@ -82,6 +82,10 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.qf_linear.argtypes = [i32, i32, i32, i32, vp, vp, vp, ctypes.c_float, vp, vp, i32, vp,
                               vp]
     lib.qf_linear_pair.argtypes = [ctypes.POINTER(LinearArgs), ctypes.POINTER(LinearArgs), vp]
+    lib.qf_linear_beside_merge.argtypes = [ctypes.POINTER(LinearArgs), i32, i32, i32, i32, vp, vp,
+                                           vp, vp, vp]
+    lib.qf_linear_attn_current.argtypes = [ctypes.POINTER(DecodeDesc), vp, vp, vp, vp, vp, vp, vp, vp,
+                                           vp, vp, vp, vp, ctypes.POINTER(LinearArgs), vp]
     lib.qf_attn_decode_split_beside.argtypes = [ctypes.POINTER(DecodeDesc), vp, vp, vp, vp, vp, vp,
                                                 vp, vp, vp, sz, ctypes.POINTER(LinearArgs), vp]
     dp = ctypes.POINTER(ctypes.c_double)
@@ -95,8 +99,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                  "qf_attn_decode_workspace_size", "qf_attn_decode", "qf_attn_decode_noalloc",
                  "qf_attn_combine", "qf_attn_combine_current", "qf_attn_combine_current_append",
                  "qf_kv_append",
-                 "qf_linear", "qf_linear_pair", "qf_attn_decode_split_beside",
-                 "qf_schedule_simulate", "qf_version"):
+                 "qf_linear", "qf_linear_pair", "qf_linear_beside_merge", "qf_linear_attn_current",
+                 "qf_attn_decode_split_beside", "qf_schedule_simulate", "qf_version"):
         getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     return lib
@@ -493,6 +497,67 @@ def linear_pair(first, second):
     stream = torch.cuda.current_stream(first["x"].device).cuda_stream
     _check(load_library().qf_linear_pair(ctypes.byref(a), ctypes.byref(b), ctypes.c_void_p(stream)))
     return out_a, out_b
+
+
+def linear_beside_merge(product, part_out, part_lse, merged_out, merged_lse):
+    """``linear(**product)`` beside the merge of the shard slots into fp32 pairs merged_out [B, Hq, D],
+    merged_lse [B, Hq] (qf_linear_beside_merge; one launch for one request); returns the product's
+    output(s)."""
+    la, result = _linear_call(**product)
+    _require(part_out, "part_out", torch.float32, 4)
+    _require(part_lse, "part_lse", torch.float32, 3)
+    _require(merged_out, "merged_out", torch.float32, 3)
+    _require(merged_lse, "merged_lse", torch.float32, 2)
+    B, S, Hq, D = part_out.shape
+    if (tuple(part_lse.shape) != (B, S, Hq) or tuple(merged_out.shape) != (B, Hq, D)
+            or tuple(merged_lse.shape) != (B, Hq)):
+        raise QFError(QF_EINVAL, "part_lse / merged_out / merged_lse shapes do not match part_out")
+    stream = torch.cuda.current_stream(part_out.device).cuda_stream
+    _check(load_library().qf_linear_beside_merge(
+        ctypes.byref(la), B, Hq, D, S, _ptr(part_out), _ptr(part_lse), _ptr(merged_out),
+        _ptr(merged_lse), ctypes.c_void_p(stream)))
+    return result
+
+
+def linear_attn_current(merged_out, merged_lse, q, k_cur, v_cur, attn, lse, k_cache, v_cache,
+                        block_table, ctx_lens, w, scale=None, residual=None, out=None, status=None,
+                        max_pages=None):
+    """One request: fold the current token into the merged pair (attn bf16 [1, Hq, D], lse fp32
+    [1, Hq], written), append it to the cache, and W . attn (+ residual), in one launch
+    (qf_linear_attn_current); returns the product's output [1, N]."""
+    _require(merged_out, "merged_out", torch.float32, 3)
+    _require(merged_lse, "merged_lse", torch.float32, 2)
+    for t, name in ((q, "q"), (k_cur, "k_cur"), (v_cur, "v_cur"), (attn, "attn")):
+        _require(t, name, torch.bfloat16, 3)
+    _require(k_cache, "k_cache", torch.bfloat16, 4)
+    _require(v_cache, "v_cache", torch.bfloat16, 4)
+    _require(ctx_lens, "ctx_lens", torch.int32, 1)
+    if lse is not None:
+        _require(lse, "lse", torch.float32, 2)
+    if block_table is not None:
+        _require(block_table, "block_table", torch.int32, 2)
+    if status is not None:
+        _require(status, "status", torch.int32)
+    B, Hq, D = q.shape
+    Hkv, P = k_cache.shape[1], k_cache.shape[2]
+    if (tuple(merged_out.shape) != (B, Hq, D) or tuple(merged_lse.shape) != (B, Hq)
+            or attn.shape != q.shape or tuple(k_cur.shape) != (B, Hkv, D)
+            or v_cur.shape != k_cur.shape or v_cache.shape != k_cache.shape
+            or k_cache.shape[3] != D or ctx_lens.shape[0] != B
+            or (lse is not None and tuple(lse.shape) != (B, Hq))):
+        raise QFError(QF_EINVAL, "merged pair / q / k_cur / v_cur / attn / cache shapes do not match")
+    if scale is None:
+        scale = D ** -0.5
+    if max_pages is None:
+        max_pages = block_table.shape[1] if block_table is not None else k_cache.shape[0] // max(B, 1)
+    la, result = _linear_call(attn.view(B, Hq * D), w, residual=residual, out=out)
+    desc = DecodeDesc(B, Hq, Hkv, D, P, int(max_pages), int(k_cache.shape[0]), 1, float(scale))
+    stream = torch.cuda.current_stream(q.device).cuda_stream
+    _check(load_library().qf_linear_attn_current(
+        ctypes.byref(desc), _ptr(merged_out), _ptr(merged_lse), _ptr(q), _ptr(k_cur), _ptr(v_cur),
+        _ptr(attn), _ptr(lse), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(ctx_lens),
+        _ptr(status), ctypes.byref(la), ctypes.c_void_p(stream)))
+    return result
 
 
 def decode_workspace_size(desc: DecodeDesc) -> int:

@@ -1,4 +1,5 @@
 // Standalone launch of the fused decode-block products (bodies in linear_body.h and linear_mfma.h).
+#include "attn_linear.h"
 #include "linear_mfma.h"
 
 namespace qf {
@@ -128,6 +129,46 @@ linear_pair_tiles_kernel(const LinearParams a, const LinearParams b, int32_t blo
                                                    ((int)blockIdx.x - blocks_a) * rows, rows, lds);
 }
 
+// The merge of one request's shard slots beside a product of one row behind the RMS prologue: the
+// product's workgroups, then one per query head.
+template <int U>
+__global__ void __launch_bounds__(lin::kThreads)
+linear_merge_kernel(const LinearParams a, int32_t blocks_a, const float* __restrict__ in_o,
+                    const float* __restrict__ in_lse, float* __restrict__ out_o,
+                    float* __restrict__ out_lse, int32_t entries, int32_t hq) {
+  if ((int)blockIdx.x < blocks_a)
+    lin::linear_rows<kProRmsNorm, 1, U, 1, false>(a.x, a.w, a.gain, a.residual, a.out_a, a.out_b, a.M,
+                                                  a.N, a.K, a.n_split, a.eps, blockIdx.x);
+  else
+    mrg::merge_row<false, false, lin::kRowsPerBlock>(in_o, in_lse, out_o, out_lse, entries, hq, 0,
+                                                     (int)blockIdx.x - blocks_a, nullptr, nullptr,
+                                                     nullptr, 1, 0.0f);
+}
+
+// W . attn of one request: the first workgroup writes the folded attention and appends the current
+// token, the others take 4 R output rows each.
+template <int U, int R>
+__global__ void __launch_bounds__(lin::kThreads)
+linear_attn_kernel(const lin::AttnFold f, const LinearParams p, uint16_t* __restrict__ attn,
+                   float* __restrict__ lse, const AppendParams a) {
+  if (blockIdx.x == 0) {
+    lin::write_fold(f, attn, lse);
+    app::append_request(a.k, a.v, a.block_table, a.ctx_lens, f.k_cur, f.v_cur, a.status, a.hkv,
+                        a.max_pages, a.num_pages, 1, 0);
+    return;
+  }
+  __shared__ uint4 s_x[64 * U];
+  lin::attn_rows<U, R>(f, p, blockIdx.x - 1, s_x);
+}
+
+template <int U>
+void launch_linear_merge_u(const LinearParams& l, const MergeParams& m, hipStream_t stream) {
+  const int blocks = lin::linear_blocks(l.N, 1);
+  hipLaunchKernelGGL((linear_merge_kernel<U>), dim3(blocks + m.hq), dim3(lin::kThreads), 0, stream, l,
+                     blocks, m.in_o, m.in_lse, static_cast<float*>(m.out_o), m.out_lse, m.entries,
+                     m.hq);
+}
+
 template <int U>
 void launch_pair_u(const LinearParams& a, const LinearParams& b, hipStream_t stream) {
   const int blocks_a = lin::linear_blocks(a.N, 1);
@@ -213,6 +254,49 @@ hipError_t launch_linear_pair(const LinearParams& a, const LinearParams& b, hipS
       default: launch_pair_tiles<5, 8, 1>(a, b, rows, stream); break;
     }
   }
+  return hipGetLastError();
+}
+
+// A product and the merge of shard slots into fp32 pairs: one launch for one request and one row behind
+// the RMS prologue, else two.
+hipError_t launch_linear_merge(const LinearParams& l, const MergeParams& m, hipStream_t stream) {
+  if (l.M != 1 || m.rows != 1 || l.prologue != kProRmsNorm || l.glu || l.N > INT32_MAX / 2) {
+    const hipError_t e = l.M > 0 ? launch_linear(l, stream) : hipSuccess;
+    return e != hipSuccess ? e : launch_merge(m, false, stream);
+  }
+  switch (lin::pick_unroll(1, l.K)) {
+    case 1: launch_linear_merge_u<1>(l, m, stream); break;
+    case 2: launch_linear_merge_u<2>(l, m, stream); break;
+    case 3: launch_linear_merge_u<3>(l, m, stream); break;
+    case 4: launch_linear_merge_u<4>(l, m, stream); break;
+    case 5: launch_linear_merge_u<5>(l, m, stream); break;
+    case 6: launch_linear_merge_u<6>(l, m, stream); break;
+    case 7: launch_linear_merge_u<7>(l, m, stream); break;
+    default: launch_linear_merge_u<8>(l, m, stream); break;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_linear_attn(const LinearParams& l, const MergeParams& m, const float* merged_lse,
+                              const AppendParams& a, hipStream_t stream) {
+  const lin::AttnFold f{m.in_o, merged_lse, m.q, m.k_cur, m.v_cur, m.hq, m.hq / m.hkv, m.scale};
+  // Every workgroup folds all heads: two rows a wavefront where there are more rows than 8 a compute
+  // unit.
+  const int rows = l.N > 2048 ? 2 : 1;
+  const dim3 grid(1 + lin::linear_blocks(l.N, rows)), block(lin::kThreads);
+  uint16_t* attn = static_cast<uint16_t*>(m.out_o);
+  auto launch = [&](auto u) {
+    constexpr int U = decltype(u)::value;
+    if (rows == 1)
+      hipLaunchKernelGGL((linear_attn_kernel<U, 1>), grid, block, 0, stream, f, l, attn, m.out_lse, a);
+    else
+      hipLaunchKernelGGL((linear_attn_kernel<U, 2>), grid, block, 0, stream, f, l, attn, m.out_lse, a);
+  };
+  const int chunks = (l.K + 511) / 512;   // of 4 heads
+  if (chunks <= 1) launch(std::integral_constant<int, 1>{});
+  else if (chunks == 2) launch(std::integral_constant<int, 2>{});
+  else if (chunks <= 4) launch(std::integral_constant<int, 4>{});
+  else launch(std::integral_constant<int, 8>{});
   return hipGetLastError();
 }
 

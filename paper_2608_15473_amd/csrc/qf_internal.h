@@ -110,6 +110,11 @@ struct LinearParams {
 };
 hipError_t launch_linear(const LinearParams& p, hipStream_t stream);
 hipError_t launch_linear_pair(const LinearParams& a, const LinearParams& b, hipStream_t stream);
+hipError_t launch_linear_merge(const LinearParams& l, const MergeParams& m, hipStream_t stream);
+// out = W . attn (+ residual) for one request, attn being the current token folded into the merged pair
+// (m.in_o, merged_lse) of its cache, written to m.out_o / m.out_lse, and the token appended (a).
+hipError_t launch_linear_attn(const LinearParams& l, const MergeParams& m, const float* merged_lse,
+                              const AppendParams& a, hipStream_t stream);
 // The sweep with the merge fused into its last workgroup per (request, KV head)
 // (decode_split.hip): p.out_o / p.out_lse hold the partial states, counters [batch * hkv] int32
 // start at zero and are left at zero.

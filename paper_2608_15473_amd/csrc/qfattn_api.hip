@@ -673,6 +673,101 @@ int qf_linear_pair(const qf_linear_args* first, const qf_linear_args* second, vo
   return QF_OK;
 }
 
+int qf_linear_beside_merge(const qf_linear_args* product, int32_t batch, int32_t n_q_heads,
+                           int32_t head_dim, int32_t max_shards, const float* part_out,
+                           const float* part_lse, float* merged_out, float* merged_lse,
+                           void* stream) {
+  g_error[0] = 0;
+  if (!product) return fail(QF_EINVAL, "product is NULL");
+  qf::LinearParams l{};
+  bool noop = false;
+  const int rc = prepare_linear(product, &l, &noop);
+  if (rc) return rc;
+  if (batch < 0) return fail(QF_EINVAL, "batch %d < 0", batch);
+  if (n_q_heads < 1 || n_q_heads > QF_MAX_Q_HEADS)
+    return fail(QF_EINVAL, "n_q_heads %d not in [1, %d]", n_q_heads, QF_MAX_Q_HEADS);
+  if (max_shards < 1) return fail(QF_EINVAL, "max_shards %d < 1", max_shards);
+  if (head_dim != qf::kHeadDim) return fail(QF_EUNSUPPORTED, "head_dim %d != %d", head_dim, qf::kHeadDim);
+  if ((int64_t)batch * n_q_heads > INT32_MAX) return fail(QF_EINVAL, "batch * n_q_heads too large");
+  if (batch > 0 && (!part_out || !part_lse || !merged_out || !merged_lse))
+    return fail(QF_EINVAL, "a required pointer is NULL");
+  if (batch > 0 && (!aligned(part_out, 16) || !aligned(merged_out, 16) || !aligned(part_lse, 4) ||
+                    !aligned(merged_lse, 4)))
+    return fail(QF_EALIGN, "part_out and merged_out must be 16-byte aligned, the log-sum-exps 4-byte");
+  qf::MergeParams m{};
+  m.in_o = part_out;
+  m.in_lse = part_lse;
+  m.out_o = merged_out;
+  m.out_lse = merged_lse;
+  m.rows = batch;
+  m.entries = max_shards;
+  m.hq = n_q_heads;
+  if (noop) l.M = 0;
+  const hipError_t e = qf::launch_linear_merge(l, m, static_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return fail(QF_EHIP, "linear + merge launch: %s", hipGetErrorString(e));
+  return QF_OK;
+}
+
+int qf_linear_attn_current(const qf_decode_desc* desc, const float* merged_out,
+                           const float* merged_lse, const void* q, const void* k_cur,
+                           const void* v_cur, void* attn, float* lse, void* k_cache, void* v_cache,
+                           const int32_t* block_table, int32_t* ctx_lens, int32_t* status,
+                           const qf_linear_args* product, void* stream) {
+  g_error[0] = 0;
+  int rc = check_desc(desc);
+  if (rc) return rc;
+  const qf_decode_desc& d = *desc;
+  if (!product) return fail(QF_EINVAL, "product is NULL");
+  if (d.batch > 1) return fail(QF_EUNSUPPORTED, "one request per call (got %d)", d.batch);
+  if (product->rows != d.batch || product->k != d.n_q_heads * d.head_dim ||
+      product->prologue != QF_LINEAR_PLAIN || product->x != attn)
+    return fail(QF_EINVAL, "the product must take attn: rows == batch, k == n_q_heads * head_dim, no "
+                           "prologue, x == attn");
+  qf::LinearParams l{};
+  bool noop = false;
+  rc = prepare_linear(product, &l, &noop);
+  if (rc || noop) return rc;
+  if (!merged_out || !merged_lse || !q || !k_cur || !v_cur || !attn || !k_cache || !v_cache ||
+      !ctx_lens)
+    return fail(QF_EINVAL, "a required pointer is NULL");
+  if (!aligned(merged_out, 16) || !aligned(q, 16) || !aligned(k_cur, 16) || !aligned(v_cur, 16) ||
+      !aligned(attn, 16))
+    return fail(QF_EALIGN, "merged_out, q, k_cur, v_cur and attn must be 16-byte aligned");
+  if (!aligned(merged_lse, 4) || (lse && !aligned(lse, 4)) || !aligned(k_cache, 4) ||
+      !aligned(v_cache, 4) || !aligned(ctx_lens, 4) || (block_table && !aligned(block_table, 4)) ||
+      (status && !aligned(status, 4)))
+    return fail(QF_EALIGN, "every other pointer must be 4-byte aligned");
+  if (!block_table && d.max_pages_per_seq > d.num_pages)
+    return fail(QF_EINVAL, "identity block table needs num_pages >= batch * max_pages_per_seq");
+  if (l.N > INT32_MAX / 2) return fail(QF_EINVAL, "n_out %d too large", l.N);
+  qf::MergeParams m{};
+  m.in_o = merged_out;
+  m.out_o = attn;
+  m.out_lse = lse;
+  m.rows = 1;
+  m.hq = d.n_q_heads;
+  m.hkv = d.n_kv_heads;
+  m.q = static_cast<const uint16_t*>(q);
+  m.k_cur = static_cast<const uint16_t*>(k_cur);
+  m.v_cur = static_cast<const uint16_t*>(v_cur);
+  m.scale = d.softmax_scale;
+  qf::AppendParams a{};
+  a.k = static_cast<uint16_t*>(k_cache);
+  a.v = static_cast<uint16_t*>(v_cache);
+  a.block_table = block_table;
+  a.ctx_lens = ctx_lens;
+  a.status = status;
+  a.batch = 1;
+  a.hkv = d.n_kv_heads;
+  a.max_pages = d.max_pages_per_seq;
+  a.num_pages = d.num_pages;
+  a.advance = 1;
+  const hipError_t e =
+      qf::launch_linear_attn(l, m, merged_lse, a, static_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return fail(QF_EHIP, "linear_attn launch: %s", hipGetErrorString(e));
+  return QF_OK;
+}
+
 int qf_attn_decode_split_beside(const qf_decode_desc* desc, const void* q, const void* k_cache,
                                 const void* v_cache, const int32_t* block_table,
                                 const int32_t* ctx_lens, const int32_t* n_shards,

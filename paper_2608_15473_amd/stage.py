@@ -20,6 +20,10 @@ the two may run at once.  On one GPU this module offers three orders of the same
                    (qf_attn_decode_split_beside), so the two share every CU: five launches a block
                    instead of seven.
 
+For one request, where every launch is latency, the merge of the shards runs beside W_k|W_v N1(z)
+(qf_linear_beside_merge) and the current-token fold and the append in W_o's launch
+(qf_linear_attn_current), in all three modes: four launches a block in "fused".
+
 Every step is one of the library's HIP kernels: the four products fused with the normalisation
 or activation that feeds them and the residual add that follows (qf_linear), the sweep, and the merge
 with the current-token fold and the cache append in one launch.  All three modes produce bitwise identical
@@ -98,6 +102,9 @@ class QFirstStack:
         self.lse = buf(B, self.hq, dtype=torch.float32)
         self.part_out = buf(B, self.max_shards, self.hq, D, dtype=torch.float32)
         self.part_lse = buf(B, self.max_shards, self.hq, dtype=torch.float32)
+        if B == 1:                                            # the merged pair of the cache
+            self.merged = buf(B, self.hq, D, dtype=torch.float32)
+            self.merged_lse = buf(B, self.hq, dtype=torch.float32)
         self.status = torch.zeros(1, dtype=torch.int32, device=self.device)
         ws = max(qf.workspace_size(qf.make_desc(self.q, c.k_cache, c.block_table,
                                                 self.max_shards, self.scale))
@@ -166,6 +173,21 @@ class QFirstStack:
                 self._linear(u, w["w_gu"], self.act, "rms_norm", w["g2"], glu_out=True)
             with self._span("W_down"):                                       # z = u + M(N2 u)
                 self._linear(self.act, w["w_down"], self.z, residual=u)
+        if B == 1:
+            # one request: the tail of the block in two launches, in every mode
+            if mode == "streams":
+                main.wait_stream(self.attn_stream)
+            with self._span("W_k,W_v + merge"):                              # k, v read z
+                qf.linear_beside_merge(
+                    dict(x=self.z, w=w["w_kv"], prologue="rms_norm", gain=w["g1"], eps=self.eps,
+                         out=self.k.view(B, -1), split=self.hkv * self.d, out_b=self.v.view(B, -1)),
+                    self.part_out, self.part_lse, self.merged, self.merged_lse)
+            with self._span("current-token fold + cache append + W_o"):     # y = z + W_o attn
+                qf.linear_attn_current(self.merged, self.merged_lse, self.q, self.k, self.v,
+                                       self.attn, self.lse, c.k_cache, c.v_cache, c.block_table,
+                                       c.ctx_lens, w["w_o"], scale=self.scale, residual=self.z,
+                                       out=out, status=self.status)
+            return out
         with self._span("W_k,W_v"):                                          # k, v read z
             self._linear(self.z, w["w_kv"], self.k.view(B, -1), "rms_norm", w["g1"],
                          out_b=self.v.view(B, -1))
