@@ -250,7 +250,8 @@ __device__ __forceinline__ void sweep_unit(
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ n_shards,
     float* __restrict__ out_o, float* __restrict__ out_lse, int32_t hq, int32_t hkv,
     int32_t max_pages, int32_t num_pages, int32_t max_shards, int32_t chunks, int32_t n_units,
-    int32_t units_per_xcd, int32_t batch, int32_t run, float scale_log2, const unsigned bid,
+    int32_t units_per_xcd, int32_t batch, int32_t run, UnitDivisors by, float scale_log2,
+    const unsigned bid,
     int32_t* __restrict__ counters = nullptr, uint16_t* __restrict__ merged_o = nullptr,
     float* __restrict__ merged_lse = nullptr, const int32_t* __restrict__ unit_order = nullptr) {
   // Which unit this workgroup sweeps.  Workgroups are dispatched in index order, round-robin over
@@ -278,17 +279,18 @@ __device__ __forceinline__ void sweep_unit(
   int pair = 0;  // long shards with chunks: index of the (request, shard, KV head) in unit order
   if (run > 0) {
     const unsigned j = bid / 8u;
-    const unsigned r = j / (unsigned)run;
+    const unsigned r = by.run.of(j);
     const unsigned i = (bid - (r + (r >> 1) + (r >> 2) + (r >> 3))) & 7u;   // XCD bid % 8, rotated
     const unsigned item_unit = (8u * r + i - r) * (unsigned)run + j;        // item * run + j % run
     if (item_unit >= (unsigned)n_units) return;
-    const int unit = (int)item_unit;
-    g = unit % hkv;
-    int rest = unit / hkv;
-    c = rest % chunks;
-    rest /= chunks;
-    s = rest % max_shards;
-    b = rest / max_shards;
+    unsigned rest = by.hkv.of(item_unit);
+    g = (int)(item_unit - rest * (unsigned)hkv);
+    unsigned q = by.chunks.of(rest);
+    c = (int)(rest - q * (unsigned)chunks);
+    rest = q;
+    q = by.shards.of(rest);
+    s = (int)(rest - q * (unsigned)max_shards);
+    b = (int)q;
   } else {
     const int unit = unit_order != nullptr ? unit_order[bid] : (int)bid;
     if (unit < 0 || unit >= n_units) return;
@@ -714,10 +716,11 @@ decode_split_kernel(const uint16_t* __restrict__ qp, const uint16_t* __restrict_
                     float* __restrict__ out_o, float* __restrict__ out_lse, int32_t hq,
                     int32_t hkv, int32_t max_pages, int32_t num_pages, int32_t max_shards,
                     int32_t chunks, int32_t n_units, int32_t units_per_xcd, int32_t batch,
-                    int32_t run, float scale_log2, const int32_t* __restrict__ unit_order) {
+                    int32_t run, UnitDivisors by, float scale_log2,
+                    const int32_t* __restrict__ unit_order) {
   sweep_unit<G, W, NBUF>(qp, kp, vp, block_table, ctx_lens, n_shards, out_o, out_lse, hq, hkv,
                          max_pages, num_pages, max_shards, chunks, n_units, units_per_xcd, batch,
-                         run, scale_log2, blockIdx.x, nullptr, nullptr, nullptr, unit_order);
+                         run, by, scale_log2, blockIdx.x, nullptr, nullptr, nullptr, unit_order);
 }
 
 // The XCD dealing cycle of rank_units_kernel: kXcdWeightEven : kXcdWeightOdd in lowest terms
@@ -909,11 +912,11 @@ decode_fused_kernel(const uint16_t* __restrict__ qp, const uint16_t* __restrict_
                     float* __restrict__ out_o, float* __restrict__ out_lse, int32_t hq,
                     int32_t hkv, int32_t max_pages, int32_t num_pages, int32_t max_shards,
                     int32_t chunks, int32_t n_units, int32_t units_per_xcd, int32_t batch,
-                    int32_t run, float scale_log2, int32_t* __restrict__ counters,
+                    int32_t run, UnitDivisors by, float scale_log2, int32_t* __restrict__ counters,
                     uint16_t* __restrict__ merged_o, float* __restrict__ merged_lse) {
   sweep_unit<G, W, NBUF, true>(qp, kp, vp, block_table, ctx_lens, n_shards, out_o, out_lse, hq,
                                hkv, max_pages, num_pages, max_shards, chunks, n_units,
-                               units_per_xcd, batch, run, scale_log2, blockIdx.x, counters,
+                               units_per_xcd, batch, run, by, scale_log2, blockIdx.x, counters,
                                merged_o, merged_lse);
 }
 
@@ -924,7 +927,7 @@ hipError_t launch_fused_g(const SplitParams& p, int32_t* counters, void* out, fl
   hipLaunchKernelGGL((decode_fused_kernel<G, kSplitWaves, kSplitBuffers>), dim3(grid),
                      dim3(64 * kSplitWaves), 0, stream, p.q, p.k, p.v, p.block_table, p.ctx_lens,
                      p.n_shards, p.out_o, p.out_lse, p.hq, p.hkv, p.max_pages, p.num_pages,
-                     p.max_shards, p.chunks, p.n_units, p.units_per_xcd, p.batch, p.run,
+                     p.max_shards, p.chunks, p.n_units, p.units_per_xcd, p.batch, p.run, p.by,
                      p.scale_log2, counters, static_cast<uint16_t*>(out), lse);
   return hipGetLastError();
 }
@@ -937,7 +940,7 @@ hipError_t launch_gn(const SplitParams& p, hipStream_t stream) {
   hipLaunchKernelGGL((decode_split_kernel<G, kSplitWaves, NBUF>), dim3(grid), dim3(64 * kSplitWaves),
                      0, stream, p.q, p.k, p.v, p.block_table, p.ctx_lens, p.n_shards, p.out_o,
                      p.out_lse, p.hq, p.hkv, p.max_pages, p.num_pages, p.max_shards, p.chunks,
-                     p.n_units, p.units_per_xcd, p.batch, p.run, p.scale_log2, p.unit_order);
+                     p.n_units, p.units_per_xcd, p.batch, p.run, p.by, p.scale_log2, p.unit_order);
   return hipGetLastError();
 }
 
@@ -965,7 +968,7 @@ sweep_beside_linear_kernel(
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ n_shards,
     float* __restrict__ out_o, float* __restrict__ out_lse, int32_t hq, int32_t hkv,
     int32_t max_pages, int32_t num_pages, int32_t max_shards, int32_t chunks, int32_t n_units,
-    int32_t units_per_xcd, int32_t batch, int32_t run, float scale_log2,
+    int32_t units_per_xcd, int32_t batch, int32_t run, UnitDivisors by, float scale_log2,
     const int32_t* __restrict__ unit_order, const uint16_t* __restrict__ x,
     const uint16_t* __restrict__ w,
     const uint16_t* __restrict__ gain, const uint16_t* __restrict__ residual,
@@ -979,7 +982,7 @@ sweep_beside_linear_kernel(
   if ((unsigned)((j + 1ull) * S / T) > before) {
     sweep_unit<G, kSplitWaves, kSplitBuffers>(qp, kp, vp, block_table, ctx_lens, n_shards, out_o,
                                               out_lse, hq, hkv, max_pages, num_pages, max_shards,
-                                              chunks, n_units, units_per_xcd, batch, run,
+                                              chunks, n_units, units_per_xcd, batch, run, by,
                                               scale_log2, 8u * before + lane8, nullptr, nullptr,
                                               nullptr, unit_order);
     return;
@@ -1051,7 +1054,7 @@ hipError_t launch_beside(const SplitParams& p, const LinearParams& l, hipStream_
   hipLaunchKernelGGL((sweep_beside_linear_kernel<G, MB>), dim3(grid), dim3(64 * kSplitWaves), 0,
                      stream, p.q, p.k, p.v, p.block_table, p.ctx_lens, p.n_shards, p.out_o,
                      p.out_lse, p.hq, p.hkv, p.max_pages, p.num_pages, p.max_shards, p.chunks,
-                     p.n_units, p.units_per_xcd, p.batch, p.run, p.scale_log2, p.unit_order,
+                     p.n_units, p.units_per_xcd, p.batch, p.run, p.by, p.scale_log2, p.unit_order,
                      l.x, l.w, l.gain,
                      l.residual, l.out_a, l.out_b, l.M, l.N, l.K, l.n_split, l.eps, l.prologue,
                      l.glu ? 1 : 0, tiles ? 1 : 0, linear_groups);

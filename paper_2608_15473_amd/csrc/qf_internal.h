@@ -32,6 +32,24 @@ constexpr int kXcdWeightOdd = 920;
 constexpr int kRankBuckets = 1024;
 constexpr int kRankMaxPairs = 8192;
 
+// Division of n < 2^31 by a launch constant d: (n * mul) >> shift with mul = ceil(2^shift / d),
+// shift = 31 + ceil(log2 d); exact, since n (mul d - 2^shift) < 2^31 d <= 2^shift.
+struct Divisor {
+  uint32_t mul = 1u << 31, shift = 31;
+  Divisor() = default;
+  explicit Divisor(uint32_t d) {
+    uint32_t l = 0;
+    while ((uint64_t(1) << l) < d) ++l;
+    shift = 31 + l;
+    mul = (uint32_t)(((uint64_t(1) << shift) + d - 1) / d);
+  }
+  __host__ __device__ uint32_t of(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
+};
+// The divisors that turn a workgroup index into a unit of the short-shard order.
+struct UnitDivisors {
+  Divisor run, hkv, chunks, shards;
+};
+
 // One launch of the sweep kernel.  A workgroup handles one unit (request b, shard s, chunk c,
 // KV head g); its output slot is [((b * max_shards + s) * chunks + c) * hq + g * G + h].
 struct SplitParams {
@@ -47,6 +65,7 @@ struct SplitParams {
   int32_t n_units;              // B * max_shards * chunks * Hkv
   // Short-shard order: units of an item, which run on one XCD; long-shard order: 0.
   int32_t run;
+  UnitDivisors by;
   int32_t units_per_xcd;        // workgroup indices per XCD: whole items (run > 0), ceil(n_units / 8)
   // The long-shard order with chunks == 1 only, or null: [8 * units_per_xcd] int32 that an ordering
   // kernel, launched just before the sweep, fills with the unit each workgroup index sweeps (-1:

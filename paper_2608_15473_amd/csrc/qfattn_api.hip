@@ -211,6 +211,10 @@ int prepare_split(const qf_decode_desc* desc, const void* q, const void* k_cache
   // whose chunk count fills exactly the resident workgroups of the two-buffer kernel, keeps two
   // buffers (deep ones would leave a second, partial round: -2% on the 131,072-position share).
   p.deep = !long_order && shard_pages >= qf::kDeepMinPages && chunks == 1;
+  p.by.run = qf::Divisor((uint32_t)std::max(p.run, 1));
+  p.by.hkv = qf::Divisor((uint32_t)d.n_kv_heads);
+  p.by.chunks = qf::Divisor((uint32_t)chunks);
+  p.by.shards = qf::Divisor((uint32_t)d.max_shards);
   p.scale_log2 = (float)((double)d.softmax_scale * 1.4426950408889634);
 
   sp->group = d.n_q_heads / d.n_kv_heads;
