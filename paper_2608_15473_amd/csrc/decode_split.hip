@@ -705,11 +705,11 @@ __device__ __forceinline__ void sweep_unit(
                         max_shards * chunks);
 }
 
-// Three wavefronts per SIMD with two page buffers (the long-shard sweep): the matrix path at G = 4
+// Three wavefronts per SIMD with two page buffers (the long-shard sweep) and with three at G <= 2: the matrix path at G = 4
 // needs the hint to stay within 168 registers (it does, without spills); deeper buffers take two.
 template <int G, int W, int NBUF>
 __global__ void __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(NBUF == 2 && G <= 4 ? 3 : 2)))
+__attribute__((amdgpu_waves_per_eu((NBUF == 2 && G <= 4) || (NBUF == 3 && G <= 2) ? 3 : 2)))
 decode_split_kernel(const uint16_t* __restrict__ qp, const uint16_t* __restrict__ kp,
                     const uint16_t* __restrict__ vp, const int32_t* __restrict__ block_table,
                     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ n_shards,
@@ -948,6 +948,8 @@ hipError_t launch_gn(const SplitParams& p, hipStream_t stream) {
 // NBUF only changes how far ahead pages are requested, never the arithmetic.
 template <int G>
 hipError_t launch_g(const SplitParams& p, hipStream_t stream) {
+  if (p.deep && G <= 2 && p.n_units < kDeepManyUnits)
+    return launch_gn<G, G <= 2 ? kFewUnitsBuffers : kSplitBuffers>(p, stream);
   if (p.deep) return launch_gn<G, split_buffers_deep(G)>(p, stream);
   return launch_gn<G, kSplitBuffers>(p, stream);
 }

@@ -9,15 +9,21 @@ namespace qf {
 constexpr int kHeadDim = 128;     // D
 constexpr int kPage = 16;         // P
 constexpr int kSplitWaves = 4;    // waves per workgroup of the sweep kernel
-// Pages in registers per wave of the sweep (1 computed, the rest in flight).  Long shards keep
-// three wavefronts per SIMD with 2.  Short shards of some length (a handful of pages per
-// wavefront, so a workgroup's life is mostly its first pages' latency) go deeper, at two
-// wavefronts per SIMD: measured on MI355X, 5 buffers make 32-page shards at G=2 2% faster, while
-// long ragged shards lose 4% at that occupancy and shards of 2-3 pages per wavefront lose up to
-// 19% (the occupancy is lost and the extra buffers stay empty).
+// Pages in registers per wave of the sweep, all in flight while the oldest is waited for.  Long shards
+// keep three wavefronts per SIMD with 2 (long ragged shards lose 4% at two wavefronts).  Short shards of
+// some length (a handful of pages per wavefront, so a workgroup's life is mostly its first pages'
+// latency) go deeper, at two wavefronts per SIMD: measured on MI355X, 32-page shards at G=2 2% faster.
+// Shorter ones keep 2: 3 pages per wavefront all at once (4,608 positions in units of 12 pages) took
+// 11.1 us a layer against 10.5.
 constexpr int kSplitBuffers = 2;
 constexpr int split_buffers_deep(int group) { return group <= 2 ? 5 : group == 4 ? 3 : 2; }
 constexpr int kDeepMinPages = 4 * kSplitWaves;   // shard pages (at full capacity) for deep buffers
+// At G <= 2, launches of fewer units than kDeepManyUnits (5 rounds of resident workgroups) take 3 buffers,
+// which keep three wavefronts per SIMD: with few rounds what is resident counts (12 ragged requests of up
+// to 7,003 positions at 16 shards 26.8 -> 25.5 us a layer, 8 requests of 4,608 at 8 shards 35.1 -> 33.9),
+// with many the depth (32 requests of 32,768 at 64 shards 676 against 661 with 5).
+constexpr int kFewUnitsBuffers = 3;
+constexpr int kDeepManyUnits = 4096;
 
 // Shards at least this long (pages, at full capacity) are swept in the long-shard order (largest
 // shard first), shorter ones in the short-shard order (dealt to the XCDs by items; decode_split.hip).
