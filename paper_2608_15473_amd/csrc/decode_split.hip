@@ -309,36 +309,6 @@ __device__ __forceinline__ void sweep_unit(
     s = max_shards - 1 - rest / batch;
   }
 
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int row = lane >> 4;
-  const int col = lane & 15;
-
-  // With 4 or 8 heads per KV head the scores come from the matrix cores (process_mf below);
-  // otherwise the VALU computes them (process_valu).  Measured: the matrix path is 1-5% faster at
-  // G = 4 and 27-32% faster at G = 8, where the VALU path spends most of its issue slots on the
-  // dot products and reductions, and 1-2.5% slower at G = 2, where the VALU has slack and the LDS
-  // round trip only adds latency.
-  constexpr bool MF = G >= 4;
-
-  // Queries of the group, requested ahead of everything that waits for the request's shape.  VALU path: dims 8col..8col+7 of every head as packed bf16 pairs.
-  // Matrix path: the queries are the 16 columns of the B operand of S^T = K Q^T (column c holds
-  // head c % G), split over the dims in 4 steps of 32: lane (row, col) holds dims
-  // 32kk + 8row .. 32kk + 8row + 7 of head col % G for step kk.
-  uint32_t qv[G][4];
-  bf16x8_t qb[4];
-  if constexpr (MF) {
-    const uint4* qrow = reinterpret_cast<const uint4*>(qp + ((size_t)b * hq + (size_t)g * G + col % G) * D);
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) qb[kk] = __builtin_bit_cast(bf16x8_t, qrow[4 * kk + row]);
-  } else {
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const uint4 t = reinterpret_cast<const uint4*>(qp + ((size_t)b * hq + (size_t)g * G + h) * D)[col];
-      qv[h][0] = t.x; qv[h][1] = t.y; qv[h][2] = t.z; qv[h][3] = t.w;
-    }
-  }
-
   // The request's shape, checked: an out-of-range value poisons this unit's log-sum-exp with NaN.
   const ShardRange range = shard_range(ctx_lens, n_shards, b, s, max_pages, max_shards);
   const int n = range.n;
@@ -379,6 +349,37 @@ __device__ __forceinline__ void sweep_unit(
       merge_if_last<G, W>(out_o, out_lse, counters, merged_o, merged_lse, b, g, hq, hkv,
                           max_shards * chunks);
     return;
+  }
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row = lane >> 4;
+  const int col = lane & 15;
+
+  // With 4 or 8 heads per KV head the scores come from the matrix cores (process_mf below);
+  // otherwise the VALU computes them (process_valu).  Measured: the matrix path is 1-5% faster at
+  // G = 4 and 27-32% faster at G = 8, where the VALU path spends most of its issue slots on the
+  // dot products and reductions, and 1-2.5% slower at G = 2, where the VALU has slack and the LDS
+  // round trip only adds latency.
+  constexpr bool MF = G >= 4;
+
+  // Queries of the group (not requested before the shape is known: 82% of a ragged batch's units are empty,
+  // and their queries cost it 0.5%).  VALU path: dims 8col..8col+7 of every head as packed bf16 pairs.
+  // Matrix path: the queries are the 16 columns of the B operand of S^T = K Q^T (column c holds
+  // head c % G), split over the dims in 4 steps of 32: lane (row, col) holds dims
+  // 32kk + 8row .. 32kk + 8row + 7 of head col % G for step kk.
+  uint32_t qv[G][4];
+  bf16x8_t qb[4];
+  if constexpr (MF) {
+    const uint4* qrow = reinterpret_cast<const uint4*>(qp + ((size_t)b * hq + (size_t)g * G + col % G) * D);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) qb[kk] = __builtin_bit_cast(bf16x8_t, qrow[4 * kk + row]);
+  } else {
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const uint4 t = reinterpret_cast<const uint4*>(qp + ((size_t)b * hq + (size_t)g * G + h) * D)[col];
+      qv[h][0] = t.x; qv[h][1] = t.y; qv[h][2] = t.z; qv[h][3] = t.w;
+    }
   }
 
   // Online-softmax state.  VALU path: every lane keeps (m, l) of all G heads for its row.  Matrix
