@@ -16,12 +16,12 @@ constexpr int kSplitWaves = 4;    // waves per workgroup of the sweep kernel
 // Shorter ones keep 2: 3 pages per wavefront all at once (4,608 positions in units of 12 pages) took
 // 11.1 us a layer against 10.5.
 constexpr int kSplitBuffers = 2;
-constexpr int split_buffers_deep(int group) { return group <= 2 ? 5 : group == 4 ? 3 : 2; }
+constexpr int split_buffers_deep(int group) { return group <= 2 ? 4 : group == 4 ? 3 : 2; }
 constexpr int kDeepMinPages = 4 * kSplitWaves;   // shard pages (at full capacity) for deep buffers
 // At G <= 2, launches of fewer units than kDeepManyUnits (5 rounds of resident workgroups) take 3 buffers,
 // which keep three wavefronts per SIMD: with few rounds what is resident counts (12 ragged requests of up
 // to 7,003 positions at 16 shards 26.8 -> 25.5 us a layer, 8 requests of 4,608 at 8 shards 35.1 -> 33.9),
-// with many the depth (32 requests of 32,768 at 64 shards 676 against 661 with 5).
+// with many the depth (32 requests of 32,768 at 64 shards 676 us with 3; 4 and 5 alike within 0.5%).
 constexpr int kFewUnitsBuffers = 3;
 constexpr int kDeepManyUnits = 4096;
 
