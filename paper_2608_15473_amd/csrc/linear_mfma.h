@@ -26,7 +26,11 @@
 // With the RMS prologue the factor x * gain has up to 16 significant bits, so it is fed exactly as two
 // bf16 halves (its upper 8 bits and the rest); r = 1 / sqrt(mean x^2 + eps) is applied at the end, as
 // on the vector path.  An infinite factor's lower half is inf - inf, and an infinite weight meets lower
-// halves that are 0: an output that comes out NaN is summed again without halves.
+// halves that are 0: such an output may come out NaN where the exact sum is infinite, so with this
+// prologue a NaN is summed again without halves.  Not where the row's sum of squares is not finite (an
+// input row that holds a NaN or an infinity, as every row after a request whose cache was refused):
+// r is then 0 or NaN and the output NaN whatever the sum was, and one such row of eight made 19,456 x
+// 2,560 outputs take 294 us instead of 21 (21 now).  What is left are infinite weights and gains.
 #pragma once
 
 #include <type_traits>
@@ -61,16 +65,11 @@ struct TileLds {
   float ss[W][2][kTileRows];                       // sums of squares (RMS prologue)
 };
 
-// One output summed by one thread as the vector path sums it (without the final factor).
-template <int PRO>
-__device__ __attribute__((noinline)) float plain_sum(const uint16_t* x, const uint16_t* w,
-                                                     const uint16_t* gain, int32_t K) {
+// One output behind the RMS prologue summed by one thread without halves (and without the final factor).
+__device__ __attribute__((noinline)) inline float plain_sum(const uint16_t* x, const uint16_t* w,
+                                                            const uint16_t* gain, int32_t K) {
   float y = 0.0f;
-  for (int k = 0; k < K; ++k) {
-    float p = lo(x[k]);
-    if (PRO == kProRmsNorm) p *= lo(gain[k]);
-    y = fmaf(lo(w[k]), p, y);
-  }
+  for (int k = 0; k < K; ++k) y = fmaf(lo(w[k]), lo(x[k]) * lo(gain[k]), y);
   return y;
 }
 
@@ -264,16 +263,6 @@ __device__ __forceinline__ void linear_tiles(
     else if constexpr (W == 8) return at(v) + at(v + 4);
     else return (at(v) + at(v + 8)) + (at(v + 4) + at(v + 12));
   };
-  auto value = [&](int n) {
-    float y = 0.0f;
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-      for (int s = 0; s < 2; ++s) y += over_waves(v, [&](int i) { return lds.sum[i][s][n][om]; });
-    if (__builtin_isnan(y))
-      y = plain_sum<PRO>(x + (size_t)om * K, w + (size_t)(n0 + n) * K, gain, K);
-    return y;
-  };
   float scale = 1.0f;
   if constexpr (RMS) {
     float t = 0.0f;
@@ -283,6 +272,17 @@ __device__ __forceinline__ void linear_tiles(
       for (int s = 0; s < 2; ++s) t += over_waves(v, [&](int i) { return lds.ss[i][s][om]; });
     scale = 1.0f / sqrtf(t / (float)K + eps);
   }
+  auto value = [&](int n) {
+    float y = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) y += over_waves(v, [&](int i) { return lds.sum[i][s][n][om]; });
+    if constexpr (RMS)
+      if (__builtin_isnan(y) && scale > 0.0f)   // a finite sum of squares
+        y = plain_sum(x + (size_t)om * K, w + (size_t)(n0 + n) * K, gain, K);
+    return y;
+  };
   const int n = n0 + on;
   if constexpr (GLU) {
     const float g = value(on) * scale, v = value(on + 1) * scale;

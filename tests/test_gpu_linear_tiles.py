@@ -101,6 +101,46 @@ def test_non_finite_inputs_come_out_as_on_the_vector_path(gpu, pro):
     torch.testing.assert_close(got[same], one[same], rtol=2 ** -7, atol=1e-4)
 
 
+@pytest.mark.parametrize("pro,N,K", [(None, 2560, 9728), ("rms_norm", 19456, 2560)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), 3e19])   # 3e19: finite, its square is not
+def test_a_bad_row_neither_changes_nor_slows_the_others(gpu, pro, N, K, bad):
+    """One row of eight that is not finite (a request marked NaN): its outputs are those of the
+    vector path, the other rows' bits are the ones they have without it, and the product takes no
+    longer than a product of finite rows (1.5 times its time, against 8 to 40 when every NaN
+    output is summed again by one thread)."""
+    x, w, g, _ = _inputs(gpu, 8, N, K, pro, False)
+    y = x.clone()
+    y[3] = bad
+    say(f"[tiles] a row of {bad}, {pro}, N={N} K={K}")
+    good, got = qf.linear(x, w, pro, g, 1e-6), qf.linear(y, w, pro, g, 1e-6)
+    one = qf.linear(y[3:4], w, pro, g, 1e-6).float()
+    keep = [m for m in range(8) if m != 3]
+    assert torch.equal(got[keep].view(torch.int16), good[keep].view(torch.int16))
+    row = got[3:4].float()
+    assert torch.equal(torch.isnan(row), torch.isnan(one))
+    fin = torch.isfinite(one)
+    assert torch.equal(row[~fin & ~torch.isnan(one)], one[~fin & ~torch.isnan(one)])
+    if pro is None:
+        torch.testing.assert_close(row[fin], one[fin], rtol=2 ** -6, atol=1e-3 * abs(3e19))
+    else:
+        assert torch.equal(row[fin], one[fin])          # a sum of squares of inf: 0 or NaN
+
+    def best(a):
+        times = []
+        for _ in range(5):
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            for _ in range(8):
+                qf.linear(a, w, pro, g, 1e-6, out=got)
+            t[1].record()
+            t[1].synchronize()
+            times.append(t[0].elapsed_time(t[1]))
+        return min(times)
+    best(x)
+    base, slow = best(x), best(y)
+    assert slow < 1.5 * base, (base, slow)
+
+
 @pytest.mark.parametrize("M,N,I,K", [(1, 2048, 3072, 1024), (1, 33, 5, 2568), (1, 8, 40, 9736),
                                      (2, 250, 7, 1032), (8, 2048, 3072, 1024), (5, 4095, 6000, 72),
                                      (8, 4096, 9728, 328), (3, 5000, 1, 64)])
