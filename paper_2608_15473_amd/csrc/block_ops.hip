@@ -26,49 +26,55 @@ linear_tiles_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__
                                         (int)blockIdx.x * rows, rows, lds);
 }
 
-template <int PRO, int T, int W, int RB, bool GLU>
-void launch_tiles(const LinearParams& p, int rows, hipStream_t stream) {
-  hipLaunchKernelGGL((linear_tiles_kernel<PRO, T, W, RB, GLU>), dim3((p.N + rows - 1) / rows),
-                     dim3(64 * W), 0, stream, p.x, p.w, p.gain, p.residual, p.out_a, p.out_b, p.M,
-                     p.N, p.K, p.n_split, p.eps, rows);
+// The output rows of a workgroup (even) for products of n and m outputs in one launch.  Up to 40 rows (5
+// tiles) for each of the 256 compute units, one workgroup a unit takes an even share; above, as few
+// workgroups a unit as keep one within `most` rows, all of one size.  `most` is 40 where five tiles leave
+// room for two workgroups on a unit (128 registers at 8 wavefronts) and 32 behind the RMS prologue
+// without GLU, where they take 143 (two rows of input, 60,000 x 1,024: 27.3 us with 40 rows, 24.0 with 32;
+// eight rows, 151,936 x 1,024: 73.3 and 54.8).  From three workgroups a unit on, they run in rounds.
+constexpr int kTileUnits = 256, kTileMost = 40;
+int tile_rows(int64_t n, int64_t m, int most) {
+  if (n + m <= kTileUnits * kTileMost) most = kTileMost;
+  const int64_t per_unit = (n + m + kTileUnits * most - 1) / (kTileUnits * most);
+  int64_t rows = ((n + m + kTileUnits * per_unit - 1) / (kTileUnits * per_unit) + 1) / 2 * 2;
+  while (rows < most && (n + rows - 1) / rows + (m + rows - 1) / rows > kTileUnits * per_unit) rows += 2;
+  return (int)rows;
 }
+constexpr int tile_most(int prologue, bool glu) { return prologue == kProRmsNorm && !glu ? 32 : kTileMost; }
 
-// The output rows of a workgroup (even) for products of n and m outputs in one launch, and the
-// workgroups per compute unit that makes: as few as keep a workgroup within 40 rows (5 tiles), all of
-// them of one size.
-struct TileShare {
-  int per_unit, rows;
-};
-TileShare tile_share(int64_t n, int64_t m) {
-  constexpr int64_t kUnits = 256, kMost = 40;
-  const int64_t per_unit = (n + m + kUnits * kMost - 1) / (kUnits * kMost);
-  int64_t rows = ((n + m + kUnits * per_unit - 1) / (kUnits * per_unit) + 1) / 2 * 2;
-  while (rows < kMost && (n + rows - 1) / rows + (m + rows - 1) / rows > kUnits * per_unit) rows += 2;
-  return {(int)per_unit, (int)rows};
+// Calls launch(T, W, RB) for workgroups of `rows` output rows, RB rounds of K in flight: 8 wavefronts,
+// without a prologue 4 for one tile (each holds more of the slots: fewer wavefronts to start, and less to
+// add at the end).  With few tiles a workgroup is alone on its unit and has more rounds in flight; from
+// three tiles on, the registers of one round let two workgroups share a unit.
+// Sixteen wavefronts kept one workgroup a unit at 128 registers (with three rounds in flight behind the RMS
+// prologue 3 of them in memory), us: 64 x 512 with two rows of input 2.54 -> 2.43, 1,024 x 3,072 4.29 -> 3.95,
+// 4,096 x 2,560 (RMS) 7.04 -> 6.51, 6,144 x 1,024 (RMS, GLU) 5.60 -> 5.16, 9,728 x 2,560 (RMS, GLU) 12.9 ->
+// 11.5; with eight rows 2.74 -> 2.56, 5.02 -> 4.77, 7.64 -> 7.24, 5.77 -> 5.23, 13.3 -> 11.9.
+template <int PRO, class Launch>
+void with_tiles(int rows, Launch&& launch) {
+  constexpr bool RMS = PRO == kProRmsNorm;
+  auto go = [&](auto t, auto w, auto rb) { launch(t, w, rb); };
+  constexpr std::integral_constant<int, 1> i1{};
+  constexpr std::integral_constant<int, 2> i2{};
+  constexpr std::integral_constant<int, 8> w8{};
+  switch ((rows + lin::kTileRows - 1) / lin::kTileRows) {
+    case 1: go(i1, std::integral_constant<int, RMS ? 8 : 4>{}, i2); break;
+    case 2: go(i2, w8, std::integral_constant<int, RMS ? 1 : 3>{}); break;
+    case 3: go(std::integral_constant<int, 3>{}, w8, i1); break;
+    case 4: go(std::integral_constant<int, 4>{}, w8, i1); break;
+    default: go(std::integral_constant<int, 5>{}, w8, i1); break;
+  }
 }
 
 template <int PRO, bool GLU>
 void launch_tiles_pro(const LinearParams& p, hipStream_t stream) {
-  const auto [per_unit, rows] = tile_share(p.N, 0);
-  const int t = (rows + lin::kTileRows - 1) / lin::kTileRows;
-  // Rounds in flight: as many as 128 registers hold (the RMS prologue also keeps the gains and the
-  // halves).
-  constexpr bool RMS = PRO == kProRmsNorm;
-  if (per_unit == 1) {
-    switch (t) {
-      case 1: launch_tiles<PRO, 1, 16, RMS ? 3 : 4, GLU>(p, rows, stream); break;
-      case 2: launch_tiles<PRO, 2, 16, RMS ? 2 : 3, GLU>(p, rows, stream); break;
-      case 3: launch_tiles<PRO, 3, 16, 2, GLU>(p, rows, stream); break;
-      case 4: launch_tiles<PRO, 4, 16, RMS ? 1 : 2, GLU>(p, rows, stream); break;
-      default: launch_tiles<PRO, 5, 16, 1, GLU>(p, rows, stream); break;
-    }
-  } else {
-    switch (t) {
-      case 3: launch_tiles<PRO, 3, 8, 1, GLU>(p, rows, stream); break;
-      case 4: launch_tiles<PRO, 4, 8, 1, GLU>(p, rows, stream); break;
-      default: launch_tiles<PRO, 5, 8, 1, GLU>(p, rows, stream); break;
-    }
-  }
+  const int rows = tile_rows(p.N, 0, tile_most(PRO, GLU));
+  with_tiles<PRO>(rows, [&](auto t, auto w, auto rb) {
+    constexpr int T = decltype(t)::value, W = decltype(w)::value, RB = decltype(rb)::value;
+    hipLaunchKernelGGL((linear_tiles_kernel<PRO, T, W, RB, GLU>), dim3((p.N + rows - 1) / rows),
+                       dim3(64 * W), 0, stream, p.x, p.w, p.gain, p.residual, p.out_a, p.out_b, p.M,
+                       p.N, p.K, p.n_split, p.eps, rows);
+  });
 }
 
 // One row per wavefront; two (a gate row and its up row) with the GLU output.
@@ -176,13 +182,6 @@ void launch_pair_u(const LinearParams& a, const LinearParams& b, hipStream_t str
                      dim3(lin::kThreads), 0, stream, a, b, blocks_a);
 }
 
-template <int T, int W, int RB>
-void launch_pair_tiles(const LinearParams& a, const LinearParams& b, int rows, hipStream_t stream) {
-  const int blocks_a = (a.N + rows - 1) / rows;
-  hipLaunchKernelGGL((linear_pair_tiles_kernel<T, W, RB>), dim3(blocks_a + (b.N + rows - 1) / rows),
-                     dim3(64 * W), 0, stream, a, b, blocks_a, rows);
-}
-
 template <int PRO>
 void launch_rows(const LinearParams& p, hipStream_t stream) {
   switch (lin::rows_bucket(p.M)) {
@@ -237,23 +236,13 @@ hipError_t launch_linear_pair(const LinearParams& a, const LinearParams& b, hipS
     }
     return hipGetLastError();
   }
-  const auto [per_unit, rows] = tile_share(a.N, b.N);
-  const int t = (rows + lin::kTileRows - 1) / lin::kTileRows;
-  if (per_unit == 1) {
-    switch (t) {
-      case 1: launch_pair_tiles<1, 16, 3>(a, b, rows, stream); break;
-      case 2: launch_pair_tiles<2, 16, 2>(a, b, rows, stream); break;
-      case 3: launch_pair_tiles<3, 16, 2>(a, b, rows, stream); break;
-      case 4: launch_pair_tiles<4, 16, 1>(a, b, rows, stream); break;
-      default: launch_pair_tiles<5, 16, 1>(a, b, rows, stream); break;
-    }
-  } else {
-    switch (t) {
-      case 3: launch_pair_tiles<3, 8, 1>(a, b, rows, stream); break;
-      case 4: launch_pair_tiles<4, 8, 1>(a, b, rows, stream); break;
-      default: launch_pair_tiles<5, 8, 1>(a, b, rows, stream); break;
-    }
-  }
+  const int rows = tile_rows(a.N, b.N, tile_most(kProRmsNorm, false));
+  const int blocks_a = (a.N + rows - 1) / rows;
+  with_tiles<kProRmsNorm>(rows, [&](auto t, auto w, auto rb) {
+    constexpr int T = decltype(t)::value, W = decltype(w)::value, RB = decltype(rb)::value;
+    hipLaunchKernelGGL((linear_pair_tiles_kernel<T, W, RB>), dim3(blocks_a + (b.N + rows - 1) / rows),
+                       dim3(64 * W), 0, stream, a, b, blocks_a, rows);
+  });
   return hipGetLastError();
 }
 

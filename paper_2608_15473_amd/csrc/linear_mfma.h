@@ -5,18 +5,19 @@
 // fused multiply-add per weight and input row.  Here one v_mfma_f32_16x16x32_bf16 takes 512 weights
 // for all input rows at once, so the product is a weight stream again.  Measured with 8 input rows
 // (vector path -> here, us a launch in a HIP graph, weights from HBM): 6,144 x 1,024 with the RMS
-// prologue 11.9 -> 5.6, 2,048 x 1,024 8.1 -> 4.1, 1,024 x 3,072 7.4 -> 4.9, 19,456 x 2,560 38.3 -> 21.0
-// (4.7 TB/s), 2,560 x 9,728 29.0 -> 13.2.  With 2 rows the two are within 5% on the small ones and here
-// is 8-21% faster on the large; with one row the vector path is faster where launches are short
-// (2,048 x 1,024: 3.4 against 3.9) and equal elsewhere.
+// prologue 12.0 -> 5.2, 2,048 x 1,024 8.2 -> 4.0, 1,024 x 3,072 7.4 -> 4.7, 19,456 x 2,560 39.0 -> 21.1
+// (4.7 TB/s), 2,560 x 9,728 29.1 -> 12.9.  With 2 rows the tiles are 1 to 46% faster but for products of
+// a few hundred outputs and inputs (64 x 512: 2.1 -> 2.4); with one row the vector path is faster where
+// launches are short (300 x 1,000: 2.6 against 3.2, 6,144 x 1,024 4.8 against 5.1, 2,048 x 1,024 3.5
+// against 3.6) and within 8% either way elsewhere.
 //
 // Tiles.  The 16 rows of the A operand are 8 output rows times 2 slices of K, and the 16 columns of
 // the B operand 8 input rows times the same slices; the product's diagonal blocks (equal slices) are
 // the sums wanted, the others are not read.  So a tile has 8 output rows, not 16, and one load
 // instruction reads 128 contiguous bytes (a cache line) of each.  A workgroup takes any number of
-// output rows up to 8 T: the launch deals them evenly over the compute units, because all workgroups
-// stream at once and the one with the most rows ends last (2,560 x 9,728: 320 workgroups of 8 rows,
-// two on a quarter of the units, took 20.3 us; 256 of 10 rows 13.2).
+// output rows up to 8 T: up to 10,240 outputs the launch deals them evenly over the compute units, one
+// workgroup each, because all of them stream at once and the one with the most rows ends last (2,560 x
+// 9,728: 320 workgroups of 8 rows, two on a quarter of the units, took 20.3 us; 256 of 10 rows 13.2).
 //
 // Sums.  K is dealt in blocks of 64 inputs to 16 slots, a round of 1,024 inputs after the other; each
 // slot's sum is one chain of matrix instructions, and the slots' sums meet in one fixed tree.  A

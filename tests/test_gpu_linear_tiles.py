@@ -1,6 +1,6 @@
 """The matrix-core products (2 to 8 input rows) at the edges of their tiles: K around a block (64), a
 round (1,024) and the rounds in flight, N that is odd, below a workgroup's share, and at every
-number of tiles per workgroup (1 to 5, and two workgroups per compute unit), through qf_linear and
+number of tiles per workgroup (1 to 5, and up to four workgroups per compute unit), through qf_linear and
 beside a sweep (another decomposition: bitwise the same).
 
 Gate: the bf16 values around the exact result widened by the fp32 accumulation bound of the other
@@ -31,7 +31,15 @@ CASES = [  # (M, N, K, prologue, residual, split, GLU output)
     (2, 10240, 136, None, True, None, False),             # 5 tiles
     (8, 10242, 2120, "rms_norm", False, None, True),      # two workgroups per compute unit: 3 tiles
     (3, 14400, 200, None, False, 7, False),               # 4 tiles
-    (8, 20000, 1992, "rms_norm", False, None, False),     # 5 tiles
+    (8, 20000, 1992, "rms_norm", False, None, False),     # three workgroups: 4 tiles
+    (3, 30000, 72, "rms_norm", False, None, False),       # four
+    (5, 9001, 2056, "rms_norm", True, None, False),       # one workgroup of 5 tiles, K in 3 rounds
+    (7, 9730, 1032, "rms_norm", False, None, True),
+    (4, 2600, 2056, None, True, None, False),             # 2 tiles, three rounds in flight: 3,
+    (2, 2601, 3080, None, False, 2600, False),            # 4, 5 and 6 rounds
+    (8, 2600, 4104, None, False, None, True),
+    (3, 2600, 5128, None, False, None, False),
+    (6, 1026, 2056, "rms_norm", False, None, True),       # 1 tile, two in flight: 3 rounds
     (8, 264, 9736, None, True, None, False),              # 10 rounds
     (5, 1026, 5128, "rms_norm", False, None, True),
 ]
