@@ -994,24 +994,31 @@ sweep_beside_linear_kernel(
   const unsigned lb = 8u * (j - before) + lane8;
   if constexpr (MB > lin::kVectorRows) {
     if (tiles) {
-      constexpr int RW = lin::kTileRows;
-      __shared__ lin::TileLds<1, kSplitWaves> lds;
-      const int n0 = (int)lb * RW;
-      if (prologue == kProRmsNorm) {
-        if (glu)
-          lin::linear_tiles<kProRmsNorm, 1, kSplitWaves, 1, true>(
-              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, lds);
-        else
-          lin::linear_tiles<kProRmsNorm, 1, kSplitWaves, 1, false>(
-              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, lds);
-      } else {
-        if (glu)
-          lin::linear_tiles<kProNone, 1, kSplitWaves, 1, true>(
-              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, lds);
-        else
-          lin::linear_tiles<kProNone, 1, kSplitWaves, 1, false>(
-              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, lds);
-      }
+      __shared__ lin::TileLds<2, kSplitWaves> lds;
+      auto tile = [&](auto t) {
+        constexpr int T = decltype(t)::value, RW = T * lin::kTileRows;
+        auto& l = reinterpret_cast<lin::TileLds<T, kSplitWaves>&>(lds);
+        const int n0 = (int)lb * RW;
+        if (prologue == kProRmsNorm) {
+          if (glu)
+            lin::linear_tiles<kProRmsNorm, T, kSplitWaves, 1, true>(
+                x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
+          else
+            lin::linear_tiles<kProRmsNorm, T, kSplitWaves, 1, false>(
+                x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
+        } else {
+          if (glu)
+            lin::linear_tiles<kProNone, T, kSplitWaves, 1, true>(
+                x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
+          else
+            lin::linear_tiles<kProNone, T, kSplitWaves, 1, false>(
+                x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
+        }
+      };
+      if (tiles == 1)
+        tile(std::integral_constant<int, 1>{});
+      else
+        tile(std::integral_constant<int, 2>{});
       return;
     }
   }
@@ -1045,12 +1052,30 @@ sweep_beside_linear_kernel(
     rows(std::integral_constant<int, U>{});
 }
 
+// Tiles of a product's workgroup beside the sweep: one, so that a long K is dealt to many workgroups, but
+// two
+//  * where the tiles one by one would be two rounds of a compute unit or more and K is short, so that
+//    starting and meeting is most of a workgroup's life (two rows beside the sweep of one request of 9,000
+//    positions, us: 6,144 x 1,024 with GLU 18.5 -> 13.2, 19,456 x 2,560 32.1 -> 27.1; 14.5 and 29.2 on the
+//    vector path.  4,096 x 2,048 12.7 -> 13.7, 4,096 x 14,336 28.7 -> 38.7);
+//  * where that leaves every workgroup of the launch a compute unit of its own (1,024 x 1,024 beside 192
+//    workgroups of the sweep 8.6 -> 7.0, vector path 7.9; 1,024 x 3,072 8.9 -> 7.7).
+// Most units of a ragged batch are empty, so the count is of what may run, not of what does.
+int beside_tiles(const SplitParams& p, const LinearParams& l) {
+  constexpr int kUnits = 256, R = lin::kTileRows;
+  const int64_t sweep = 8 * (int64_t)p.units_per_xcd;
+  const bool rounds = l.N > 2 * kUnits * R && l.K <= 4096;
+  const bool own = sweep + (l.N + R - 1) / R > kUnits && sweep + (l.N + 2 * R - 1) / (2 * R) <= kUnits;
+  return rounds || own ? 2 : 1;
+}
+
 template <int G, int MB>
 hipError_t launch_beside(const SplitParams& p, const LinearParams& l, hipStream_t stream) {
-  const bool tiles = lin::takes_tiles(l);
+  const int tiles = lin::takes_tiles(l) ? beside_tiles(p, l) : 0;
   const int rows = l.glu ? lin::beside_rows_glu(MB) : lin::beside_rows(MB);
-  const int linear_groups = ((tiles ? (l.N + lin::kTileRows - 1) / lin::kTileRows
-                                    : lin::linear_blocks(l.N, rows)) + 7) / 8;
+  const int per_group = tiles * lin::kTileRows;
+  const int linear_groups =
+      ((tiles ? (l.N + per_group - 1) / per_group : lin::linear_blocks(l.N, rows)) + 7) / 8;
   const unsigned grid = 8u * ((unsigned)p.units_per_xcd + (unsigned)linear_groups);
   const hipError_t e = launch_rank(p, stream);
   if (e != hipSuccess) return e;
@@ -1060,7 +1085,7 @@ hipError_t launch_beside(const SplitParams& p, const LinearParams& l, hipStream_
                      p.n_units, p.units_per_xcd, p.batch, p.run, p.by, p.scale_log2, p.unit_order,
                      l.x, l.w, l.gain,
                      l.residual, l.out_a, l.out_b, l.M, l.N, l.K, l.n_split, l.eps, l.prologue,
-                     l.glu ? 1 : 0, tiles ? 1 : 0, linear_groups);
+                     l.glu ? 1 : 0, tiles, linear_groups);
   return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """The matrix-core products (2 to 8 input rows) at the edges of their tiles: K around a block (64), a
 round (1,024) and the rounds in flight, N that is odd, below a workgroup's share, and at every
 number of tiles per workgroup (1 to 5, and up to four workgroups per compute unit), through qf_linear and
-beside a sweep (another decomposition: bitwise the same).
+beside a sweep (another decomposition, of one tile a workgroup or two: bitwise the same).
 
 Gate: the bf16 values around the exact result widened by the fp32 accumulation bound of the other
 product tests, (K/64 + 32) 2^-24 of the absolute sum.  Infinities and NaN in x, the gains and the
@@ -41,6 +41,9 @@ CASES = [  # (M, N, K, prologue, residual, split, GLU output)
     (3, 2600, 5128, None, False, None, False),
     (6, 1026, 2056, "rms_norm", False, None, True),       # 1 tile, two in flight: 3 rounds
     (8, 264, 9736, None, True, None, False),              # 10 rounds
+    (2, 4201, 4168, None, False, None, False),            # beside a sweep: one tile, 526 workgroups
+    (2, 4201, 4096, None, False, None, False),            # two tiles, 263
+    (3, 1985, 520, "rms_norm", False, 1984, False),       # one tile, all on units of their own
     (5, 1026, 5128, "rms_norm", False, None, True),
 ]
 
