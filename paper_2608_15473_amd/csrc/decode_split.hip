@@ -1022,9 +1022,11 @@ sweep_beside_linear_kernel(
       return;
     }
   }
-  // One input row: three chunks of K in a group where there are more than two (W_down of 3,072 inputs
-  // has 6: groups of two leave the launch waiting three times, of four load two chunks past the end;
-  // Qwen3-0.6B step, one request: 723 us with two, 695 with three, 711 with four).
+  // One input row: K in groups of three chunks of 512 from 1,024 to 10,240 inputs, else of two.  Fewer waits
+  // are worth the loads past the end that three may add: one row beside the sweep of one request of 4,608
+  // positions, us with groups of two and three: 1,024 x 2,048 7.43 / 7.35, 2,048 x 2,560 9.62 / 9.22, 1,024 x
+  // 3,072 8.05 / 7.41, 2,560 x 4,096 11.6 / 11.2, 2,560 x 9,728 20.4 / 17.9, but 4,096 x 14,336 29.7 / 30.2,
+  // where many groups hide a wait.
   auto rows = [&](auto unroll) {
     constexpr int UU = decltype(unroll)::value;
     if (glu) {
@@ -1046,7 +1048,7 @@ sweep_beside_linear_kernel(
       lin::linear_rows<kProNone, MB, UU, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split,
                                             eps, lb);
   };
-  if (MB == 1 && K > 1024)
+  if (MB == 1 && K > 1024 && K <= 10240)
     rows(std::integral_constant<int, MB == 1 ? 3 : U>{});
   else
     rows(std::integral_constant<int, U>{});

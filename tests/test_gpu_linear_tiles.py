@@ -91,6 +91,22 @@ def test_tiles_match_the_oracle_and_the_shared_launch(gpu, M, N, K, pro, res, sp
     assert ok.all(), (np.argwhere(~ok)[:4], out[~ok][:4], ref[~ok][:4])
 
 
+@pytest.mark.parametrize("K", [1016, 1024, 1032, 1536, 2048, 2560, 10240, 10248, 11776])
+@pytest.mark.parametrize("pro,glu", [(None, False), ("rms_norm", True)])
+def test_one_row_beside_a_sweep_equals_the_call_bitwise(gpu, K, pro, glu):
+    """The groups of chunks of a single row's K in the shared launch (two or three, whole or not)."""
+    x, w, g, r = _inputs(gpu, 1, 78, K, pro, not glu)
+    kw = dict(x=x, w=w, prologue=pro, gain=g, residual=r, glu_out=glu)
+    case = make_case(2, 4, 2, [300, 17], [2, 1], seed=3, device=gpu)
+    say(f"[tiles] one row beside a sweep, K={K} {pro} glu={glu}")
+    got = qf.attn_decode_split_beside(case.q, case.k_cache, case.v_cache, case.block_table,
+                                      case.ctx_lens, case.n_shards, kw, max_shards=2,
+                                      scale=case.scale)[2]
+    want = qf.linear(**kw)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
 @pytest.mark.parametrize("pro", [None, "rms_norm"])
 def test_non_finite_inputs_come_out_as_on_the_vector_path(gpu, pro):
     M, N, K = 6, 40, 1160
