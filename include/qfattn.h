@@ -178,12 +178,13 @@ int qf_attn_decode_split_unfolded(const qf_decode_desc* desc, const void* q, con
  *                    Values as for qf_attn_combine.
  *   workspace        device buffer of at least qf_attn_decode_workspace_size() bytes (the
  *                    partial states), 16-byte aligned; no initialisation needed.
- *   counters         int32 device array of n_counters >= B * Hkv entries, 4-byte aligned, one
- *                    per (request, KV head).  It must be ZERO-FILLED before its first use; every
- *                    call leaves the entries it used at zero again, so an array zero-filled once
- *                    serves any number of calls with any descriptor (as long as it is large
- *                    enough).  Calls that share a workspace or counters must not run
- *                    concurrently.
+ *   counters         int32 device array of n_counters >= B * Hkv entries, 4-byte aligned.  All of it
+ *                    must be ZERO-FILLED before its first use; every call leaves it at zero again, so
+ *                    an array zero-filled once serves any number of calls with any descriptor (as
+ *                    long as it is large enough).  A call uses one entry per (request, KV head):
+ *                    the first B * Hkv, or every 32nd (a cache line each, which short shards are
+ *                    faster with) if n_counters >= 32 * B * Hkv.  Calls that share a workspace or
+ *                    counters must not run concurrently.
  * Returns the codes of qf_attn_decode_split; QF_EINVAL also for a NULL out, workspace or
  * counters, a workspace that is too small or too few counters.
  */

@@ -576,7 +576,8 @@ def attn_decode(q, k_cache, v_cache, block_table, ctx_lens, n_shards, max_shards
 
     ``workspace``: uint8 tensor of at least ``decode_workspace_size`` bytes (allocated when
     None); ``counters``: int32 tensor of at least B * Hkv entries, zero-filled before its first
-    use (every call leaves it at zero; allocated zeroed when None)."""
+    use (every call leaves it at zero; with 32 * B * Hkv entries short shards are faster, which is
+    what is allocated, zeroed, when None, up to 65,536 entries)."""
     _require(q, "q", torch.bfloat16, 3)
     _require(k_cache, "k_cache", torch.bfloat16, 4)
     _require(v_cache, "v_cache", torch.bfloat16, 4)
@@ -606,7 +607,9 @@ def attn_decode(q, k_cache, v_cache, block_table, ctx_lens, n_shards, max_shards
                                 device=q.device)
     _require(workspace, "workspace", torch.uint8)
     if counters is None:
-        counters = torch.zeros(B * k_cache.shape[1], dtype=torch.int32, device=q.device)
+        groups = B * k_cache.shape[1]
+        counters = torch.zeros(groups * (32 if groups <= 2048 else 1), dtype=torch.int32,
+                               device=q.device)
     _require(counters, "counters", torch.int32)
     stream = torch.cuda.current_stream(q.device).cuda_stream
     _check(load_library().qf_attn_decode(

@@ -194,21 +194,20 @@ __device__ __forceinline__ void merge_if_last(const float* __restrict__ part_o,
                                               int32_t* __restrict__ counters,
                                               uint16_t* __restrict__ merged_o,
                                               float* __restrict__ merged_lse, int b, int g,
-                                              int hq, int hkv, int entries) {
+                                              int hq, int hkv, int entries, int counter_step) {
   __shared__ int s_last;
+  int32_t* const counter = &counters[((size_t)b * hkv + g) * counter_step];
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's partial stores are complete
   __syncthreads();
   if (threadIdx.x == 0) {
-    const int prev = __hip_atomic_fetch_add(&counters[(size_t)b * hkv + g], 1, __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
+    const int prev = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_last = (prev == entries - 1);
   }
   __syncthreads();
   if (!s_last) return;
   merge_group<G, W>(part_o, part_lse, merged_o, merged_lse, b, g, hq, entries);
   if (threadIdx.x == 0)
-    __hip_atomic_store(&counters[(size_t)b * hkv + g], 0, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Pages [p0, p1) of shard s of request b (the split rule of the interface: K = ceil(pages / S_b)
@@ -253,7 +252,8 @@ __device__ __forceinline__ void sweep_unit(
     int32_t units_per_xcd, int32_t batch, int32_t run, UnitDivisors by, float scale_log2,
     const unsigned bid,
     int32_t* __restrict__ counters = nullptr, uint16_t* __restrict__ merged_o = nullptr,
-    float* __restrict__ merged_lse = nullptr, const int32_t* __restrict__ unit_order = nullptr) {
+    float* __restrict__ merged_lse = nullptr, const int32_t* __restrict__ unit_order = nullptr,
+    int32_t counter_step = 1) {
   // Which unit this workgroup sweeps.  Workgroups are dispatched in index order, round-robin over
   // the 8 XCDs.
   //  * Short shards (run > 0): items of `run` units (the KV heads of some consecutive (shard, chunk)
@@ -347,7 +347,7 @@ __device__ __forceinline__ void sweep_unit(
     }
     if constexpr (MERGE)
       merge_if_last<G, W>(out_o, out_lse, counters, merged_o, merged_lse, b, g, hq, hkv,
-                          max_shards * chunks);
+                          max_shards * chunks, counter_step);
     return;
   }
 
@@ -703,7 +703,7 @@ __device__ __forceinline__ void sweep_unit(
   }
   if constexpr (MERGE)
     merge_if_last<G, W>(out_o, out_lse, counters, merged_o, merged_lse, b, g, hq, hkv,
-                        max_shards * chunks);
+                        max_shards * chunks, counter_step);
 }
 
 // Three wavefronts per SIMD with two page buffers (the long-shard sweep) and with three at G <= 2: the matrix path at G = 4
@@ -914,22 +914,23 @@ decode_fused_kernel(const uint16_t* __restrict__ qp, const uint16_t* __restrict_
                     int32_t hkv, int32_t max_pages, int32_t num_pages, int32_t max_shards,
                     int32_t chunks, int32_t n_units, int32_t units_per_xcd, int32_t batch,
                     int32_t run, UnitDivisors by, float scale_log2, int32_t* __restrict__ counters,
-                    uint16_t* __restrict__ merged_o, float* __restrict__ merged_lse) {
+                    uint16_t* __restrict__ merged_o, float* __restrict__ merged_lse,
+                    int32_t counter_step) {
   sweep_unit<G, W, NBUF, true>(qp, kp, vp, block_table, ctx_lens, n_shards, out_o, out_lse, hq,
                                hkv, max_pages, num_pages, max_shards, chunks, n_units,
                                units_per_xcd, batch, run, by, scale_log2, blockIdx.x, counters,
-                               merged_o, merged_lse);
+                               merged_o, merged_lse, nullptr, counter_step);
 }
 
 template <int G>
-hipError_t launch_fused_g(const SplitParams& p, int32_t* counters, void* out, float* lse,
-                          hipStream_t stream) {
+hipError_t launch_fused_g(const SplitParams& p, int32_t* counters, int32_t counter_step, void* out,
+                          float* lse, hipStream_t stream) {
   const unsigned grid = 8u * (unsigned)p.units_per_xcd;
   hipLaunchKernelGGL((decode_fused_kernel<G, kSplitWaves, kSplitBuffers>), dim3(grid),
                      dim3(64 * kSplitWaves), 0, stream, p.q, p.k, p.v, p.block_table, p.ctx_lens,
                      p.n_shards, p.out_o, p.out_lse, p.hq, p.hkv, p.max_pages, p.num_pages,
                      p.max_shards, p.chunks, p.n_units, p.units_per_xcd, p.batch, p.run, p.by,
-                     p.scale_log2, counters, static_cast<uint16_t*>(out), lse);
+                     p.scale_log2, counters, static_cast<uint16_t*>(out), lse, counter_step);
   return hipGetLastError();
 }
 
@@ -1156,13 +1157,13 @@ hipError_t launch_decode_split_beside(const SplitParams& p, int group, const Lin
   }
 }
 
-hipError_t launch_decode_fused(const SplitParams& p, int group, int32_t* counters, void* out,
-                               float* lse, hipStream_t stream) {
+hipError_t launch_decode_fused(const SplitParams& p, int group, int32_t* counters,
+                               int32_t counter_step, void* out, float* lse, hipStream_t stream) {
   switch (group) {
-    case 1: return launch_fused_g<1>(p, counters, out, lse, stream);
-    case 2: return launch_fused_g<2>(p, counters, out, lse, stream);
-    case 4: return launch_fused_g<4>(p, counters, out, lse, stream);
-    case 8: return launch_fused_g<8>(p, counters, out, lse, stream);
+    case 1: return launch_fused_g<1>(p, counters, counter_step, out, lse, stream);
+    case 2: return launch_fused_g<2>(p, counters, counter_step, out, lse, stream);
+    case 4: return launch_fused_g<4>(p, counters, counter_step, out, lse, stream);
+    case 8: return launch_fused_g<8>(p, counters, counter_step, out, lse, stream);
     default: return hipErrorInvalidValue;
   }
 }

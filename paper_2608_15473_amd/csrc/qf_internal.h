@@ -141,10 +141,12 @@ hipError_t launch_linear_merge(const LinearParams& l, const MergeParams& m, hipS
 hipError_t launch_linear_attn(const LinearParams& l, const MergeParams& m, const float* merged_lse,
                               const AppendParams& a, hipStream_t stream);
 // The sweep with the merge fused into its last workgroup per (request, KV head)
-// (decode_split.hip): p.out_o / p.out_lse hold the partial states, counters [batch * hkv] int32
-// start at zero and are left at zero.
-hipError_t launch_decode_fused(const SplitParams& p, int group, int32_t* counters, void* out,
-                               float* lse, hipStream_t stream);
+// (decode_split.hip): p.out_o / p.out_lse hold the partial states; the counter of request b and KV head g
+// is counters[(b * hkv + g) * counter_step], zero before and after.
+hipError_t launch_decode_fused(const SplitParams& p, int group, int32_t* counters,
+                               int32_t counter_step, void* out, float* lse, hipStream_t stream);
+// Counters this far apart lie in cache lines of their own (128 bytes).
+constexpr int kCounterStep = 32;
 // The sweep and a fused product in one launch (decode_split.hip).
 hipError_t launch_decode_split_beside(const SplitParams& p, int group, const LinearParams& l,
                                       hipStream_t stream);

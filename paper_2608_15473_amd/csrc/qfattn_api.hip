@@ -104,6 +104,14 @@ int32_t units_per_item(const qf_decode_desc* d, int64_t chunks) {
   return 1;
 }
 
+// The deal of p's units in items of `run` (0: the long-shard order).
+void deal(qf::SplitParams* p, int32_t run) {
+  p->run = run;
+  p->units_per_xcd = run > 0 ? (int32_t)(((p->n_units + (int64_t)run - 1) / run + 7) / 8 * run)
+                             : (int32_t)(((int64_t)p->n_units + 7) / 8);
+  p->by.run = qf::Divisor((uint32_t)std::max(run, 1));
+}
+
 // An unchunked long-shard sweep (of up to kRankMaxPairs (request, shard) pairs) takes its units in
 // the order of rank_units_kernel, which it keeps in the workspace: one int32 per workgroup index.
 bool ranks_units(const qf_decode_desc* d, int64_t chunks) {
@@ -199,9 +207,7 @@ int prepare_split(const qf_decode_desc* desc, const void* q, const void* k_cache
   p.chunks = (int32_t)chunks;
   p.n_units = (int32_t)units;
   const bool long_order = long_shards(&d, chunks);
-  p.run = long_order ? 0 : units_per_item(&d, chunks);
-  p.units_per_xcd =
-      (int32_t)(p.run > 0 ? ((units + p.run - 1) / p.run + 7) / 8 * p.run : (units + 7) / 8);
+  deal(&p, long_order ? 0 : units_per_item(&d, chunks));
   const int64_t shard_pages = (d.max_pages_per_seq + d.max_shards - 1) / d.max_shards / chunks;
   p.unit_order = rank ? reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + state_bytes)
                       : nullptr;
@@ -211,7 +217,6 @@ int prepare_split(const qf_decode_desc* desc, const void* q, const void* k_cache
   // whose chunk count fills exactly the resident workgroups of the two-buffer kernel, keeps two
   // buffers (deep ones would leave a second, partial round: -2% on the 131,072-position share).
   p.deep = !long_order && shard_pages >= qf::kDeepMinPages && chunks == 1;
-  p.by.run = qf::Divisor((uint32_t)std::max(p.run, 1));
   p.by.hkv = qf::Divisor((uint32_t)d.n_kv_heads);
   p.by.chunks = qf::Divisor((uint32_t)chunks);
   p.by.shards = qf::Divisor((uint32_t)d.max_shards);
@@ -480,7 +485,16 @@ int decode_fused(const qf_decode_desc* desc, const void* q, const void* k_cache,
     if (e != hipSuccess) return fail(QF_EHIP, "merge launch: %s", hipGetErrorString(e));
     return QF_OK;
   }
-  const hipError_t e = qf::launch_decode_fused(sp.p, sp.group, counters, out, lse, s);
+  // Every workgroup of a group adds one to its counter.  A line that holds the counters of many groups
+  // moves between the XCDs with each addition, and many short units wait for it: so the counters are
+  // spread where the caller's array has room, and where it has not, each XCD takes a contiguous range of
+  // units, so that a line meets few of them at a time.  Measured (contiguous and packed / items and
+  // packed / items and spread, us): 23 requests of 3,895 positions at 38 shards, 2 KV heads of one query
+  // head 22.2 / 25.6 / 21.7; 20 of 3,000 at 40, 4 KV heads 28.5 / 35.3 / 28.2; 32 of 32,768 at 64, 8 of two
+  // 688 / 718 / 690; 12 ragged ones of up to 7,003 at 16, 8 of two 34.6 / 27.2 / 27.5.
+  const int32_t step = n_counters / qf::kCounterStep >= groups ? qf::kCounterStep : 1;
+  if (step == 1 && sp.p.run > 0) deal(&sp.p, (sp.p.n_units + 7) / 8);
+  const hipError_t e = qf::launch_decode_fused(sp.p, sp.group, counters, step, out, lse, s);
   if (e != hipSuccess) return fail(QF_EHIP, "decode launch: %s", hipGetErrorString(e));
   return QF_OK;
 }
