@@ -28,6 +28,10 @@ constexpr int kDeepManyUnits = 4096;
 // Shards at least this long (pages, at full capacity) are swept in the long-shard order (largest
 // shard first), shorter ones in the short-shard order (dealt to the XCDs by items; decode_split.hip).
 constexpr int kLongShardPages = 128;
+// Items of the short-shard order (units_per_item in qfattn_api.hip).
+constexpr int kDealManyUnits = 4096;
+constexpr int kDealFewUnits = 256;
+constexpr int kDealItemUnits = 8;
 // Relative page shares of the sub-shard chunks of a long shard that run on even- and odd-numbered
 // XCDs (decode_split.hip): the odd XCDs stream slower.
 constexpr int kXcdWeightEven = 1080;

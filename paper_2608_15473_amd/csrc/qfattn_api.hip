@@ -86,21 +86,31 @@ bool long_shards(const qf_decode_desc* d, int64_t chunks) {
   return shard_pages >= qf::kLongShardPages;
 }
 
-// Units of one item of the short-shard order (decode_split.hip).  Of one request, and where there are
-// many units (8 rounds of resident workgroups at G = 8, 5 at G = 2 and 4): every KV head of slots / 8
-// consecutive (shard, chunk) slots, so that a request's slots are spread over the 8 XCDs and each XCD
-// still meets few block-table lines and queries (their first read on an XCD is a miss that a short
-// workgroup cannot hide: with single slots dealt round, one request of 5,049 positions at 2 KV heads
-// took 13.9 us a layer instead of 12.7, and 16 requests of 32,768 positions at G = 8 370 instead of 365).
-// Fewer units of several requests: one slot, since their lengths may differ and a few long requests'
-// slots must not meet on one XCD (12 requests of 27 to 7,003 positions 28.3 -> 27.5 us a layer, 7 of 10
-// to 2,723 at 42 shards 24.6 -> 22.6; batches of one length lose 0-0.5%).  Fewer slots where an XCD would
-// get over an eighth more than the mean; single units where single slots still do.
+// Units of one item of the short-shard order (decode_split.hip): every KV head of some consecutive (shard,
+// chunk) slots.
+//  * One request, and many units (kDealManyUnits: 8 rounds of resident workgroups at G = 8, 5 at G = 2 and
+//    4): an eighth of a request's slots, so that they are spread over the 8 XCDs and each XCD still meets
+//    few block-table lines and queries (their first read on an XCD is a miss that a short workgroup cannot
+//    hide: with single slots dealt round, one request of 5,049 positions at 2 KV heads took 13.9 us a layer
+//    instead of 12.7, and 16 requests of 32,768 positions at G = 8 370 instead of 365).  A request of few
+//    units (kDealFewUnits: one per compute unit) takes them whether even or not, since none waits for
+//    another: 1,721 positions at 26 shards, 2 KV heads 8.9 -> 7.6 us.
+//  * Fewer units of several requests: slots of kDealItemUnits units, since their lengths may differ and a
+//    few long requests' slots must not meet on one XCD (12 requests of 27 to 7,003 positions, 8 KV heads,
+//    28.3 -> 27.5 us a layer, 7 of 10 to 2,723 at 42 shards 24.6 -> 22.6; batches of one length lose 0-0.5%).
+//    Single slots of few KV heads would share lines of the table and of the slots' log-sum-exps among the
+//    XCDs: 40 requests of 1,500 positions at 16 shards, 2 KV heads of one query head 18.7 -> 16.9 us, 30 of
+//    5,000 at 40, one KV head 21.1 -> 19.3; ragged ones of up to 7,000 positions within 2%.
+// Fewer slots where an XCD would get over an eighth more than the mean; single units where single slots
+// still do.
 int32_t units_per_item(const qf_decode_desc* d, int64_t chunks) {
   const int64_t slots = (int64_t)d->max_shards * chunks, all = slots * d->batch;
-  const bool local = d->batch == 1 || all * d->n_kv_heads >= 4096;
-  for (int64_t k = local ? (slots + 7) / 8 : 1; k > 0; --k)
-    if (((all + k - 1) / k + 7) / 8 * k * 64 <= all * 9) return (int32_t)(k * d->n_kv_heads);
+  const int64_t units = all * d->n_kv_heads, hkv = d->n_kv_heads;
+  const bool local = d->batch == 1 || units >= qf::kDealManyUnits;
+  int64_t k = local ? (slots + 7) / 8 : (qf::kDealItemUnits + hkv - 1) / hkv;
+  if (d->batch == 1 && units <= qf::kDealFewUnits) return (int32_t)(k * hkv);
+  for (; k > 0; --k)
+    if (((all + k - 1) / k + 7) / 8 * k * 64 <= all * 9) return (int32_t)(k * hkv);
   return 1;
 }
 

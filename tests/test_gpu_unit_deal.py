@@ -1,9 +1,15 @@
-"""The short-shard sweep's deal of units to XCDs (items of all KV heads of a (request, shard, chunk),
-or of single units, in rotated rows of 8) at the sizes where it can lose or repeat a unit: item
-counts around multiples of 8 and around the rule between the two item sizes, KV head counts that
-are no power of two.  Every unit's output is checked against the fp64 oracle at the parity gates,
-over buffers that hold NaN before the call, and the one-launch decode (whose count of finished units
-would hang the merge or run it early if one were lost) against the two calls."""
+"""The short-shard sweep's deal of units to XCDs (items of all KV heads of some consecutive (shard,
+chunk) slots, or of single units, in rotated rows of 8) at the sizes where it can lose or repeat a
+unit: item counts around multiples of 8, items of one slot and of several with a partial last one, on
+both sides of the rules between the item sizes (whose constants are read from the sources, so that
+a moved threshold moves no case to another item size unseen), KV head counts that are no power of two.
+Every unit's output is checked against the fp64 oracle at the parity gates, over buffers that hold
+NaN before the call, and the one-launch decode (whose count of finished units would hang the merge or
+run it early if one were lost) against the two calls.  Then every number of pages of a wavefront, for
+each depth of the page buffers."""
+
+import os
+import re
 
 import numpy as np
 import pytest
@@ -15,25 +21,48 @@ from workloads import make_case
 
 pytestmark = pytest.mark.gpu
 
+CONST = dict(re.findall(r"constexpr int (k\w+) = (\d+);", open(os.path.join(
+    os.path.dirname(qf.__file__), "csrc", "qf_internal.h")).read()))
+MANY, FEW, ITEM, DEEP_MANY = (int(CONST[k]) for k in ("kDealManyUnits", "kDealFewUnits",
+                                                      "kDealItemUnits", "kDeepManyUnits"))
 
-@pytest.mark.parametrize("batch,shards,hkv,G", [
-    (1, 1, 1, 1), (1, 7, 3, 2), (3, 3, 2, 4), (9, 7, 3, 1), (8, 8, 5, 1), (5, 13, 3, 2), (13, 9, 7, 2),
-    (72, 1, 11, 1),
+
+def _slots_per_item(batch, slots, hkv):
+    """The rule between the item sizes, restated (0: single units)."""
+    n, units = batch * slots, batch * slots * hkv
+    k = -(-slots // 8) if batch == 1 or units >= MANY else -(-ITEM // hkv)
+    if batch == 1 and units <= FEW:
+        return k
+    while k and -(-(-(-n // k)) // 8) * k * 64 > n * 9:
+        k -= 1
+    return k
+
+
+@pytest.mark.parametrize("batch,shards,hkv,G,item", [
+    (1, 1, 1, 1, 1), (1, 7, 3, 2, 1), (3, 3, 2, 4, 0), (9, 7, 3, 1, 2), (8, 8, 5, 1, 2), (5, 13, 3, 2, 3),
+    (13, 9, 7, 2, 2), (72, 1, 11, 1, 1),
+    (1, 65, 3, 1, 9), (1, 26, 2, 1, 4),       # few units of one request: an eighth, the last item short
+    (1, 300, 8, 2, 38), (1, 43, 7, 4, 6),     # more: an eighth where even
+    (1, 42, 7, 1, 0),                         # and where no number of slots is
+    (7, 13, 1, 2, 6), (11, 9, 2, 1, 1),       # several requests, few KV heads
+    (23, 29, 7, 1, 4),                        # many units of several requests, 167 items
 ])
-def test_every_unit_is_swept_once(gpu, batch, shards, hkv, G):
+def test_every_unit_is_swept_once(gpu, batch, shards, hkv, G, item):
     rng = np.random.default_rng(1000 * batch + shards)
     ctx = rng.integers(0, 40 * shards, size=batch)
     ctx[0] = 40 * shards
     case = make_case(batch, G * hkv, hkv, ctx, np.minimum(shards, 1 + ctx // 16), seed=900 + batch,
                      max_shards=shards, device=gpu)
-    say(f"[deal] batch {batch}, {shards} shards, {hkv} KV heads, G {G}")
+    chunks = qf.split_chunks(qf.make_desc(case.q, case.k_cache, case.block_table, shards, case.scale))
+    assert _slots_per_item(batch, shards * chunks, hkv) == item
+    say(f"[deal] batch {batch}, {shards} shards, {hkv} KV heads, G {G}, items of {item} slots")
     got = run_gpu(case)
     check(case, got, oracle_ref(case), label="deal")
     out, lse = qf.attn_decode(case.q, case.k_cache, case.v_cache, case.block_table, case.ctx_lens,
                               case.n_shards, max_shards=shards, scale=case.scale)
     torch.cuda.synchronize()
     np.testing.assert_allclose(lse.cpu().numpy(), got["lse"], rtol=1e-6, atol=1e-6)
-    if qf.split_chunks(qf.make_desc(case.q, case.k_cache, case.block_table, shards, case.scale)) == 1:
+    if chunks == 1 and shards <= 64:
         assert np.array_equal(out.view(torch.int16).cpu().numpy(), got["out_bits"])
 
 
