@@ -37,8 +37,8 @@ def test_group_sizes_ragged(gpu, G):
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_deep_buffers_ragged(gpu, G):
-    """The deep-buffer sweep (short shards of 16+ pages, no sub-shard chunks: NBUF 5 at G <= 2,
-    3 at G = 4) on ragged requests with partial last pages and shards of every length the split
+    """The deep-buffer sweep (short shards of 16+ pages, no sub-shard chunks: three page buffers at
+    G <= 4 in a launch of this few units) on ragged requests with partial last pages and shards of every length the split
     rule gives, every output checked."""
     rng = np.random.default_rng(190 + G)
     ctx = rng.integers(1, 3001, size=48)

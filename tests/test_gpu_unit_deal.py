@@ -66,18 +66,26 @@ def test_every_unit_is_swept_once(gpu, batch, shards, hkv, G, item):
         assert np.array_equal(out.view(torch.int16).cpu().numpy(), got["out_bits"])
 
 
-@pytest.mark.parametrize("G", [1, 2, 4, 8])
-@pytest.mark.parametrize("max_pages", [48, 128])   # the deep short-shard buffers, the long-shard ones
-def test_every_number_of_pages_per_wavefront(gpu, G, max_pages):
+@pytest.mark.parametrize("G,max_pages,repeat", [
+    (1, 48, 1), (2, 48, 1),      # three page buffers (few units of short shards at G <= 2)
+    (1, 48, 4), (2, 48, 4),      # four (many units)
+    (4, 48, 1), (8, 48, 1),      # three at G = 4, two at G = 8
+    (1, 128, 1), (2, 128, 1), (4, 128, 1), (8, 128, 1),      # long shards: two
+])
+def test_every_number_of_pages_per_wavefront(gpu, G, max_pages, repeat):
     """One shard per request of 1 to 48 pages (0 to 12 per wavefront), whole and partial: the page
-    buffers' first group, loop and end at every remainder.  Sampled heads, at the parity gates."""
-    pages = np.arange(1, 49)
-    ctx = 16 * pages - (pages * 7) % 16
+    buffers' first group, loop and end at every remainder, for each depth of the buffers.  Sampled
+    heads, at the parity gates."""
+    pages = np.tile(np.arange(1, 49), repeat)
+    ctx = 16 * pages - (pages * 7 + np.arange(len(pages)) // 48 * 5) % 16
     hkv = 24                                           # enough units for unchunked shards
-    case = make_case(48, G * hkv, hkv, ctx, 1, seed=950 + G, max_pages=max_pages, device=gpu)
+    units = 48 * repeat * hkv
+    assert (units >= DEEP_MANY) == (repeat == 4) and units // repeat < DEEP_MANY
+    case = make_case(48 * repeat, G * hkv, hkv, ctx, 1, seed=950 + G, max_pages=max_pages, device=gpu)
     desc = qf.make_desc(case.q, case.k_cache, case.block_table, 1, case.scale)
     assert qf.split_chunks(desc) == 1
-    say(f"[deal] 1 to 48 pages, G {G}, capacity {max_pages}")
-    pairs = [(b, (b * 5 + i * (G * hkv // 4 + 1)) % (G * hkv)) for b in range(48) for i in range(4)]
+    say(f"[deal] 1 to 48 pages, G {G}, capacity {max_pages}, {units} units")
+    rows = [b + 48 * (b % repeat) for b in range(48)]   # of each page count, one request
+    pairs = [(b, (b * 5 + i * (G * hkv // 4 + 1)) % (G * hkv)) for b in rows for i in range(4)]
     got = run_gpu(case)
     check(case, got, oracle_ref(case, pairs), pairs, label="pages")
