@@ -102,10 +102,12 @@ bool long_shards(const qf_decode_desc* d, int64_t chunks) {
 //    XCDs: 40 requests of 1,500 positions at 16 shards, 2 KV heads of one query head 18.7 -> 16.9 us, 30 of
 //    5,000 at 40, one KV head 21.1 -> 19.3; ragged ones of up to 7,000 positions within 2%.
 // Fewer slots where an XCD would get over an eighth more than the mean; single units where single slots
-// still do.
+// still do.  Above kDealMostUnits one contiguous range per XCD, which pads the grid by no workgroup: a
+// launch takes 2^24 - 1 of them, and 6,223 requests of 337 shards at 8 KV heads are 2^24 - 8.
 int32_t units_per_item(const qf_decode_desc* d, int64_t chunks) {
   const int64_t slots = (int64_t)d->max_shards * chunks, all = slots * d->batch;
   const int64_t units = all * d->n_kv_heads, hkv = d->n_kv_heads;
+  if (units > qf::kDealMostUnits) return (int32_t)((units + 7) / 8);
   const bool local = d->batch == 1 || units >= qf::kDealManyUnits;
   int64_t k = local ? (slots + 7) / 8 : (qf::kDealItemUnits + hkv - 1) / hkv;
   if (d->batch == 1 && units <= qf::kDealFewUnits) return (int32_t)(k * hkv);

@@ -89,3 +89,29 @@ def test_every_number_of_pages_per_wavefront(gpu, G, max_pages, repeat):
     pairs = [(b, (b * 5 + i * (G * hkv // 4 + 1)) % (G * hkv)) for b in rows for i in range(4)]
     got = run_gpu(case)
     check(case, got, oracle_ref(case, pairs), pairs, label="pages")
+
+
+@pytest.mark.slow
+def test_as_many_units_as_a_launch_takes(gpu):
+    """2^24 - 8 units of a short-shard sweep (a launch takes 2^24 - 1 workgroups of 256 threads): no
+    workgroup more than units.  Three requests hold positions; bitwise those three alone."""
+    B, S, H = 6223, 337, 8
+    live = [0, 3000, B - 1]
+    few = make_case(3, H, H, [5392, 17, 2048], S, seed=990, max_pages=S, device=gpu)
+    table = torch.full((B, S), -1, dtype=torch.int32, device=gpu)
+    ctx = torch.zeros(B, dtype=torch.int32, device=gpu)
+    q = torch.zeros(B, H, 128, dtype=torch.bfloat16, device=gpu)
+    table[live], ctx[live], q[live] = few.block_table, few.ctx_lens, few.q
+    say(f"[deal] {B * S * H} units")
+    po, pl = qf.attn_decode_split(q, few.k_cache, few.v_cache, table, ctx, S, max_shards=S,
+                                  scale=few.scale)
+    ref_o, ref_l = qf.attn_decode_split(few.q, few.k_cache, few.v_cache, few.block_table,
+                                        few.ctx_lens, few.n_shards, max_shards=S, scale=few.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(pl[live].view(torch.int32), ref_l.view(torch.int32))
+    some = torch.isfinite(ref_l)
+    assert torch.equal(po[live][some].view(torch.int32), ref_o[some].view(torch.int32))
+    pl[live] = float("-inf")
+    assert bool((pl == float("-inf")).all())
+    del po, ref_o
+    torch.cuda.empty_cache()
