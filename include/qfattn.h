@@ -345,6 +345,9 @@ int qf_schedule_simulate(int32_t n_requests, const double* arrival, const double
  * out [rows, n_split], the rest to out_b [rows, n_out - n_split] (one product can fill k and v);
  * residual: bf16 [rows, n_out] or NULL.  fp32 arithmetic, one round-to-nearest-even per output;
  * out must not alias x or residual.  Device pointers, caller-owned; asynchronous on `stream`.
+ * A row's outputs never depend on the other rows' values.  With PLAIN and RMS_NORM the order of a row's
+ * sums is one for 2 to 8 rows, whichever of them it is, and another for a single row, so the last bits of
+ * a row by itself may differ from those it has among others; with SWIGLU there is one order.
  * prologue | QF_LINEAR_GLU_OUT: the rows of W alternate the feed-forward's gate and up
  * projections (row 2i = W_gate row i, row 2i + 1 = W_up row i), and the output is the activation
  * itself, out[m, i] = silu(y[m, 2i]) * y[m, 2i + 1], bf16 [rows, n_out / 2] (computed once per

@@ -87,6 +87,11 @@ class QFirstStack:
             self.layers.append(lw)
         self.caches = list(caches)
         self.B = int(caches[0].ctx_lens.shape[0])
+        # The products take at most 8 rows a call; even shares (9 requests: 5 and 4) leave no request a
+        # call of its own, whose sums are in another order than those of 2 to 8 rows.
+        calls = -(-self.B // 8)
+        ends = [self.B * i // calls for i in range(calls + 1)] if calls else [0]
+        self.rows = list(zip(ends, ends[1:]))
         self.attn_stream = torch.cuda.Stream(self.device)    # default priority
         B, H, I, D = self.B, self.hidden, self.inter, self.d
 
@@ -125,11 +130,10 @@ class QFirstStack:
                              workspace=self.workspace)
 
     def _linear(self, x, w, out, prologue=None, gain=None, residual=None, out_b=None,
-                glu_out=False):
-        """qf_linear over the batch in blocks of at most 8 rows."""
-        B, split = self.B, out.shape[-1] if out_b is not None else None
-        for r in range(0, B, 8):
-            e = min(B, r + 8)
+                glu_out=False, first=0):
+        """qf_linear over the batch, from its share ``first`` on."""
+        split = out.shape[-1] if out_b is not None else None
+        for r, e in self.rows[first:]:
             qf.linear(x[r:e], w, prologue, gain, self.eps,
                       residual=None if residual is None else residual[r:e], out=out[r:e],
                       split=split, out_b=None if out_b is None else out_b[r:e], glu_out=glu_out)
@@ -143,22 +147,20 @@ class QFirstStack:
         main = torch.cuda.current_stream(self.device)
         if mode == "fused":
             with self._span("W_q + W_gate,W_up"):                            # both read u
-                for r in range(0, B, 8):
-                    e = min(B, r + 8)
+                for r, e in self.rows:
                     qf.linear_pair(
                         dict(x=u[r:e], w=w["w_q"], prologue="rms_norm", gain=w["g1"], eps=self.eps,
                              out=self.q[r:e].view(e - r, -1)),
                         dict(x=u[r:e], w=w["w_gu"], prologue="rms_norm", gain=w["g2"],
                              eps=self.eps, out=self.act[r:e], glu_out=True))
-            head = min(B, 8)
+            head = self.rows[0][1] if self.rows else 0
             with self._span("sweep + W_down"):                               # z = u + M(N2 u)
                 qf.attn_decode_split_beside(
                     self.q, c.k_cache, c.v_cache, c.block_table, c.ctx_lens, c.n_shards,
                     dict(x=self.act[:head], w=w["w_down"], residual=u[:head], out=self.z[:head]),
                     max_shards=self.max_shards, scale=self.scale, part_out=self.part_out,
                     part_lse=self.part_lse, workspace=self.workspace)
-                if B > head:
-                    self._linear(self.act[head:], w["w_down"], self.z[head:], residual=u[head:])
+                self._linear(self.act, w["w_down"], self.z, residual=u, first=1)
         else:
             with self._span("W_q"):                                          # q reads u
                 self._linear(u, w["w_q"], self.q.view(B, -1), "rms_norm", w["g1"])

@@ -91,6 +91,23 @@ def test_tiles_match_the_oracle_and_the_shared_launch(gpu, M, N, K, pro, res, sp
     assert ok.all(), (np.argwhere(~ok)[:4], out[~ok][:4], ref[~ok][:4])
 
 
+@pytest.mark.parametrize("N,K,pro,glu", [(64, 512, None, False), (1024, 3072, None, False),
+                                         (6144, 1032, "rms_norm", True), (9000, 1024, "rms_norm", False),
+                                         (300, 1000, "swiglu", False)])
+def test_a_row_has_the_same_bits_among_any_others(gpu, N, K, pro, glu):
+    """2 to 8 rows, in any place (and alone with the SwiGLU input): each row bitwise as among eight."""
+    gen = torch.Generator(device=gpu).manual_seed(N + K)
+    x = torch.randn(8, 2 * K if pro == "swiglu" else K, generator=gen, device=gpu).to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=gen, device=gpu) / K ** 0.5).to(torch.bfloat16)
+    g = (torch.rand(K, generator=gen, device=gpu) + 0.5).to(torch.bfloat16) if pro == "rms_norm" else None
+    say(f"[tiles] rows among others, N={N} K={K} {pro} glu={glu}")
+    full = qf.linear(x, w, pro, g, 1e-6, glu_out=glu).view(torch.int16)
+    for m in range(1 if pro == "swiglu" else 2, 8):
+        for at in (0, 8 - m):
+            got = qf.linear(x[at:at + m], w, pro, g, 1e-6, glu_out=glu).view(torch.int16)
+            assert torch.equal(got, full[at:at + m]), (m, at)
+
+
 @pytest.mark.parametrize("K", [1016, 1024, 1032, 1536, 2048, 2560, 10240, 10248, 11776])
 @pytest.mark.parametrize("pro,glu", [(None, False), ("rms_norm", True)])
 def test_one_row_beside_a_sweep_equals_the_call_bitwise(gpu, K, pro, glu):

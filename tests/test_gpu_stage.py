@@ -43,17 +43,17 @@ SHARDS = [3, 1, 1]
 SPARE = 8
 
 
-def _build(gpu, L=SHAPE.layers, seed=500, ctx=CTX, shards=SHARDS):
-    Hq, Hkv = SHAPE.n_q_heads, SHAPE.n_kv_heads
+def _build(gpu, L=SHAPE.layers, seed=500, ctx=CTX, shards=SHARDS, shape=SHAPE):
+    Hq, Hkv = shape.n_q_heads, shape.n_kv_heads
     layers, caches = [], []
     for l in range(L):
-        layers.append({k: t.to(gpu) for k, t in block_weights(SHAPE, seed + l).items()})
+        layers.append({k: t.to(gpu) for k, t in block_weights(shape, seed + l).items()})
         c = make_case(len(ctx), Hq, Hkv, np.asarray(ctx) + SPARE, shards, seed=seed + 100 + l,
                       device=gpu)
         c.ctx_lens -= SPARE
         caches.append(LayerCache(c.k_cache, c.v_cache, c.block_table, c.ctx_lens, c.n_shards))
     stack = QFirstStack(layers, caches, Hq, Hkv, max_shards=int(np.max(shards)), scale=SCALE)
-    u = block_input(len(ctx), SHAPE.hidden, seed=seed + 999).to(gpu)
+    u = block_input(len(ctx), shape.hidden, seed=seed + 999).to(gpu)
     return stack, u
 
 
@@ -218,8 +218,8 @@ def test_all_modes_equal_the_serial_order_bitwise(gpu):
 
 
 def test_more_than_eight_requests_in_all_modes(gpu):
-    """Ten requests: every product runs in blocks of 8 rows and only the first block of
-    W_gate|W_up shares the sweep's launch; the three orders still agree bitwise."""
+    """Ten requests: every product runs in two calls of 5 rows and only the first one of W_down
+    shares the sweep's launch; the three orders still agree bitwise."""
     ctx = [300, 2, 0, 45, 1000, 17, 64, 5, 129, 700]
     stack, u = _build(gpu, L=2, seed=650, ctx=ctx, shards=[3, 1, 1, 2, 4, 1, 1, 1, 2, 3])
     saved = _state(stack)
@@ -234,6 +234,28 @@ def test_more_than_eight_requests_in_all_modes(gpu):
         assert torch.equal(ys["serial"], ys[mode]), mode
         assert _same_state(states["serial"], states[mode]), mode
     assert torch.isfinite(ys["serial"].float()).all()
+
+
+@pytest.mark.parametrize("mode", ["fused", "serial"])
+def test_nine_requests_in_any_order_give_the_same_rows(gpu, mode):
+    """No request of a batch takes another path than the others (the ninth had a call of its own):
+    the same requests in another order give bitwise the same outputs and caches."""
+    ctx = [300, 2, 0, 45, 1000, 17, 64, 5, 129]
+    shape = BlockShape("wide", hidden=1024, inter=3072, n_q_heads=16, n_kv_heads=8, layers=4)
+    stack, u = _build(gpu, L=4, seed=660, ctx=ctx, shards=[3, 1, 1, 2, 4, 1, 1, 1, 2], shape=shape)
+    order = torch.tensor([8, 3, 5, 0, 7, 1, 2, 6, 4], device=gpu)
+    caches = [LayerCache(c.k_cache.clone(), c.v_cache.clone(), c.block_table[order].contiguous(),
+                         c.ctx_lens[order].contiguous(), c.n_shards[order].contiguous())
+              for c in stack.caches]
+    other = QFirstStack(stack.layers, caches, shape.n_q_heads, shape.n_kv_heads,
+                        max_shards=stack.max_shards, scale=SCALE)
+    say(f"[stage] nine requests in two orders, mode {mode}")
+    a = stack.step(u, mode=mode)
+    b = other.step(u[order].contiguous(), mode=mode)
+    torch.cuda.synchronize()
+    assert torch.equal(a[order], b)
+    for c, d in zip(stack.caches, caches):
+        assert torch.equal(c.k_cache, d.k_cache) and torch.equal(c.v_cache, d.v_cache)
 
 
 @pytest.mark.parametrize("mode", ["fused", "streams", "serial"])
