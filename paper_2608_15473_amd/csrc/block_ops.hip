@@ -182,20 +182,23 @@ void launch_pair_u(const LinearParams& a, const LinearParams& b, hipStream_t str
                      dim3(lin::kThreads), 0, stream, a, b, blocks_a);
 }
 
-template <int PRO>
-void launch_rows(const LinearParams& p, hipStream_t stream) {
-  switch (lin::rows_bucket(p.M)) {
-    case 1: launch_pro<PRO, 1>(p, stream); break;
-    case 2: launch_pro<PRO, 2>(p, stream); break;
-    case 4: launch_pro<PRO, 4>(p, stream); break;
-    default: launch_pro<PRO, 8>(p, stream); break;
-  }
-}
-
 }  // namespace
 
 hipError_t launch_linear(const LinearParams& p, hipStream_t stream) {
   if (p.M == 0 || p.N == 0) return hipSuccess;
+  if (lin::takes_single_rows(p)) {
+    for (int m = 0; m < p.M; ++m) {
+      LinearParams row = p;
+      row.M = 1;
+      row.x += (size_t)m * p.K;
+      if (p.residual) row.residual += (size_t)m * p.N;
+      row.out_a += (size_t)m * (p.glu ? p.N / 2 : p.n_split);
+      if (p.out_b) row.out_b += (size_t)m * (p.N - p.n_split);
+      const hipError_t e = launch_linear(row, stream);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   if (lin::takes_tiles(p)) {
     if (p.prologue == kProRmsNorm)
       p.glu ? launch_tiles_pro<kProRmsNorm, true>(p, stream) : launch_tiles_pro<kProRmsNorm, false>(p, stream);
@@ -203,12 +206,14 @@ hipError_t launch_linear(const LinearParams& p, hipStream_t stream) {
       p.glu ? launch_tiles_pro<kProNone, true>(p, stream) : launch_tiles_pro<kProNone, false>(p, stream);
     return hipGetLastError();
   }
-  if (p.prologue == kProRmsNorm)
-    launch_rows<kProRmsNorm>(p, stream);
-  else if (p.prologue == kProSwiglu)
-    launch_rows<kProSwiglu>(p, stream);
-  else
-    launch_rows<kProNone>(p, stream);
+  if (p.prologue == kProRmsNorm) launch_pro<kProRmsNorm, 1>(p, stream);
+  else if (p.prologue == kProNone) launch_pro<kProNone, 1>(p, stream);
+  else switch (lin::rows_bucket(p.M)) {
+    case 1: launch_pro<kProSwiglu, 1>(p, stream); break;
+    case 2: launch_pro<kProSwiglu, 2>(p, stream); break;
+    case 4: launch_pro<kProSwiglu, 4>(p, stream); break;
+    default: launch_pro<kProSwiglu, 8>(p, stream); break;
+  }
   return hipGetLastError();
 }
 
@@ -217,7 +222,7 @@ hipError_t launch_linear(const LinearParams& p, hipStream_t stream) {
 hipError_t launch_linear_pair(const LinearParams& a, const LinearParams& b, hipStream_t stream) {
   const bool pair = a.M > 0 && a.M == b.M && a.K == b.K && a.prologue == kProRmsNorm &&
                     b.prologue == kProRmsNorm && !a.glu && b.glu &&
-                    lin::takes_tiles(a) == lin::takes_tiles(b) && (a.M == 1 || lin::takes_tiles(a)) &&
+                    (a.M == 1 || lin::takes_tiles(a)) &&
                     (int64_t)a.N + b.N <= INT32_MAX / 2;
   if (!pair) {
     const hipError_t e = launch_linear(a, stream);

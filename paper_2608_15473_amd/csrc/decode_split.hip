@@ -249,8 +249,7 @@ __device__ __forceinline__ void sweep_unit(
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ n_shards,
     float* __restrict__ out_o, float* __restrict__ out_lse, int32_t hq, int32_t hkv,
     int32_t max_pages, int32_t num_pages, int32_t max_shards, int32_t chunks, int32_t n_units,
-    int32_t units_per_xcd, int32_t batch, int32_t run, UnitDivisors by, float scale_log2,
-    const unsigned bid,
+    int32_t batch, int32_t run, UnitDivisors by, float scale_log2, const unsigned bid,
     int32_t* __restrict__ counters = nullptr, uint16_t* __restrict__ merged_o = nullptr,
     float* __restrict__ merged_lse = nullptr, const int32_t* __restrict__ unit_order = nullptr,
     int32_t counter_step = 1) {
@@ -716,12 +715,11 @@ decode_split_kernel(const uint16_t* __restrict__ qp, const uint16_t* __restrict_
                     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ n_shards,
                     float* __restrict__ out_o, float* __restrict__ out_lse, int32_t hq,
                     int32_t hkv, int32_t max_pages, int32_t num_pages, int32_t max_shards,
-                    int32_t chunks, int32_t n_units, int32_t units_per_xcd, int32_t batch,
-                    int32_t run, UnitDivisors by, float scale_log2,
-                    const int32_t* __restrict__ unit_order) {
+                    int32_t chunks, int32_t n_units, int32_t batch, int32_t run, UnitDivisors by,
+                    float scale_log2, const int32_t* __restrict__ unit_order) {
   sweep_unit<G, W, NBUF>(qp, kp, vp, block_table, ctx_lens, n_shards, out_o, out_lse, hq, hkv,
-                         max_pages, num_pages, max_shards, chunks, n_units, units_per_xcd, batch,
-                         run, by, scale_log2, blockIdx.x, nullptr, nullptr, nullptr, unit_order);
+                         max_pages, num_pages, max_shards, chunks, n_units, batch, run, by,
+                         scale_log2, blockIdx.x, nullptr, nullptr, nullptr, unit_order);
 }
 
 // The XCD dealing cycle of rank_units_kernel: kXcdWeightEven : kXcdWeightOdd in lowest terms
@@ -912,13 +910,13 @@ decode_fused_kernel(const uint16_t* __restrict__ qp, const uint16_t* __restrict_
                     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ n_shards,
                     float* __restrict__ out_o, float* __restrict__ out_lse, int32_t hq,
                     int32_t hkv, int32_t max_pages, int32_t num_pages, int32_t max_shards,
-                    int32_t chunks, int32_t n_units, int32_t units_per_xcd, int32_t batch,
-                    int32_t run, UnitDivisors by, float scale_log2, int32_t* __restrict__ counters,
+                    int32_t chunks, int32_t n_units, int32_t batch, int32_t run, UnitDivisors by,
+                    float scale_log2, int32_t* __restrict__ counters,
                     uint16_t* __restrict__ merged_o, float* __restrict__ merged_lse,
                     int32_t counter_step) {
   sweep_unit<G, W, NBUF, true>(qp, kp, vp, block_table, ctx_lens, n_shards, out_o, out_lse, hq,
                                hkv, max_pages, num_pages, max_shards, chunks, n_units,
-                               units_per_xcd, batch, run, by, scale_log2, blockIdx.x, counters,
+                               batch, run, by, scale_log2, blockIdx.x, counters,
                                merged_o, merged_lse, nullptr, counter_step);
 }
 
@@ -929,8 +927,8 @@ hipError_t launch_fused_g(const SplitParams& p, int32_t* counters, int32_t count
   hipLaunchKernelGGL((decode_fused_kernel<G, kSplitWaves, kSplitBuffers>), dim3(grid),
                      dim3(64 * kSplitWaves), 0, stream, p.q, p.k, p.v, p.block_table, p.ctx_lens,
                      p.n_shards, p.out_o, p.out_lse, p.hq, p.hkv, p.max_pages, p.num_pages,
-                     p.max_shards, p.chunks, p.n_units, p.units_per_xcd, p.batch, p.run, p.by,
-                     p.scale_log2, counters, static_cast<uint16_t*>(out), lse, counter_step);
+                     p.max_shards, p.chunks, p.n_units, p.batch, p.run, p.by, p.scale_log2, counters,
+                     static_cast<uint16_t*>(out), lse, counter_step);
   return hipGetLastError();
 }
 
@@ -942,7 +940,7 @@ hipError_t launch_gn(const SplitParams& p, hipStream_t stream) {
   hipLaunchKernelGGL((decode_split_kernel<G, kSplitWaves, NBUF>), dim3(grid), dim3(64 * kSplitWaves),
                      0, stream, p.q, p.k, p.v, p.block_table, p.ctx_lens, p.n_shards, p.out_o,
                      p.out_lse, p.hq, p.hkv, p.max_pages, p.num_pages, p.max_shards, p.chunks,
-                     p.n_units, p.units_per_xcd, p.batch, p.run, p.by, p.scale_log2, p.unit_order);
+                     p.n_units, p.batch, p.run, p.by, p.scale_log2, p.unit_order);
   return hipGetLastError();
 }
 
@@ -961,8 +959,12 @@ hipError_t launch_g(const SplitParams& p, hipStream_t stream) {
 // feed-forward, §3).  Groups of 8 consecutive workgroup indices (one per XCD) are dealt to the two
 // roles in proportion to their sizes, so both start together and each keeps its index modulo 8;
 // every workgroup does exactly what it would do in its own launch.
+// MB: rows of a product on the vector path, one or several behind the SwiGLU prologue; products on the
+// tiles, of any number of rows, are in the kernels of kTilesBucket.
 // The occupancy the sweep alone reaches (registers), asked of the shared kernel too, so that
 // the product's role does not lower it.
+constexpr int kTilesBucket = 2;
+
 template <int G, int MB>
 __global__ void __launch_bounds__(64 * kSplitWaves)
 __attribute__((amdgpu_waves_per_eu(G >= 8 ? 2 : 3)))
@@ -986,73 +988,71 @@ sweep_beside_linear_kernel(
   if ((unsigned)((j + 1ull) * S / T) > before) {
     sweep_unit<G, kSplitWaves, kSplitBuffers>(qp, kp, vp, block_table, ctx_lens, n_shards, out_o,
                                               out_lse, hq, hkv, max_pages, num_pages, max_shards,
-                                              chunks, n_units, units_per_xcd, batch, run, by,
+                                              chunks, n_units, batch, run, by,
                                               scale_log2, 8u * before + lane8, nullptr, nullptr,
                                               nullptr, unit_order);
     return;
   }
-  constexpr int U = 2, R = lin::beside_rows(MB), RG = lin::beside_rows_glu(MB);
+  constexpr int R = lin::beside_rows(MB);
   const unsigned lb = 8u * (j - before) + lane8;
-  if constexpr (MB > lin::kVectorRows) {
-    if (tiles) {
-      __shared__ lin::TileLds<2, kSplitWaves> lds;
-      auto tile = [&](auto t) {
-        constexpr int T = decltype(t)::value, RW = T * lin::kTileRows;
-        auto& l = reinterpret_cast<lin::TileLds<T, kSplitWaves>&>(lds);
-        const int n0 = (int)lb * RW;
-        if (prologue == kProRmsNorm) {
-          if (glu)
-            lin::linear_tiles<kProRmsNorm, T, kSplitWaves, 1, true>(
-                x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
-          else
-            lin::linear_tiles<kProRmsNorm, T, kSplitWaves, 1, false>(
-                x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
-        } else {
-          if (glu)
-            lin::linear_tiles<kProNone, T, kSplitWaves, 1, true>(
-                x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
-          else
-            lin::linear_tiles<kProNone, T, kSplitWaves, 1, false>(
-                x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
-        }
-      };
-      if (tiles == 1)
-        tile(std::integral_constant<int, 1>{});
-      else
-        tile(std::integral_constant<int, 2>{});
-      return;
-    }
+  if (MB > 1 && (MB > kTilesBucket || tiles == 0)) {   // several rows behind the SwiGLU prologue
+    lin::linear_rows<kProSwiglu, MB, 2, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
+    return;
   }
-  // One input row: K in groups of three chunks of 512 from 1,024 to 10,240 inputs, else of two.  Fewer waits
-  // are worth the loads past the end that three may add: one row beside the sweep of one request of 4,608
-  // positions, us with groups of two and three: 1,024 x 2,048 7.43 / 7.35, 2,048 x 2,560 9.62 / 9.22, 1,024 x
-  // 3,072 8.05 / 7.41, 2,560 x 4,096 11.6 / 11.2, 2,560 x 9,728 20.4 / 17.9, but 4,096 x 14,336 29.7 / 30.2,
-  // where many groups hide a wait.
-  auto rows = [&](auto unroll) {
-    constexpr int UU = decltype(unroll)::value;
-    if (glu) {
-      if (prologue == kProRmsNorm)
-        lin::linear_rows<kProRmsNorm, MB, UU, RG, true>(x, w, gain, residual, out_a, out_b, M, N, K,
-                                                        n_split, eps, lb);
-      else
-        lin::linear_rows<kProNone, MB, UU, RG, true>(x, w, gain, residual, out_a, out_b, M, N, K,
-                                                     n_split, eps, lb);
-      return;
-    }
-    if (prologue == kProRmsNorm)
-      lin::linear_rows<kProRmsNorm, MB, UU, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split,
-                                               eps, lb);
-    else if (prologue == kProSwiglu)
-      lin::linear_rows<kProSwiglu, MB, UU, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split,
-                                              eps, lb);
+  if constexpr (MB == kTilesBucket) {
+    __shared__ lin::TileLds<2, kSplitWaves> lds;
+    auto tile = [&](auto t) {
+      constexpr int T = decltype(t)::value, RW = T * lin::kTileRows;
+      auto& l = reinterpret_cast<lin::TileLds<T, kSplitWaves>&>(lds);
+      const int n0 = (int)lb * RW;
+      if (prologue == kProRmsNorm) {
+        if (glu)
+          lin::linear_tiles<kProRmsNorm, T, kSplitWaves, 1, true>(
+              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
+        else
+          lin::linear_tiles<kProRmsNorm, T, kSplitWaves, 1, false>(
+              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
+      } else {
+        if (glu)
+          lin::linear_tiles<kProNone, T, kSplitWaves, 1, true>(
+              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
+        else
+          lin::linear_tiles<kProNone, T, kSplitWaves, 1, false>(
+              x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, n0, RW, l);
+      }
+    };
+    if (tiles == 1)
+      tile(std::integral_constant<int, 1>{});
     else
-      lin::linear_rows<kProNone, MB, UU, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split,
-                                            eps, lb);
-  };
-  if (MB == 1 && K > 1024 && K <= 10240)
-    rows(std::integral_constant<int, MB == 1 ? 3 : U>{});
-  else
-    rows(std::integral_constant<int, U>{});
+      tile(std::integral_constant<int, 2>{});
+  } else if constexpr (MB == 1) {
+    // K in groups of three chunks of 512 from 1,024 to 10,240 inputs, else of two.  Fewer waits are worth
+    // the loads past the end that three may add: one row beside the sweep of one request of 4,608
+    // positions, us with groups of two and three: 1,024 x 2,048 7.43 / 7.35, 2,048 x 2,560 9.62 / 9.22,
+    // 1,024 x 3,072 8.05 / 7.41, 2,560 x 4,096 11.6 / 11.2, 2,560 x 9,728 20.4 / 17.9, but 4,096 x 14,336
+    // 29.7 / 30.2, where many groups hide a wait.
+    auto rows = [&](auto unroll) {
+      constexpr int U = decltype(unroll)::value;
+      if (glu) {
+        if (prologue == kProRmsNorm)
+          lin::linear_rows<kProRmsNorm, 1, U, R, true>(x, w, gain, residual, out_a, out_b, M, N, K, n_split,
+                                                       eps, lb);
+        else
+          lin::linear_rows<kProNone, 1, U, R, true>(x, w, gain, residual, out_a, out_b, M, N, K, n_split,
+                                                    eps, lb);
+      } else if (prologue == kProRmsNorm) {
+        lin::linear_rows<kProRmsNorm, 1, U, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
+      } else if (prologue == kProSwiglu) {
+        lin::linear_rows<kProSwiglu, 1, U, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
+      } else {
+        lin::linear_rows<kProNone, 1, U, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
+      }
+    };
+    if (K > 1024 && K <= 10240)
+      rows(std::integral_constant<int, 3>{});
+    else
+      rows(std::integral_constant<int, 2>{});
+  }
 }
 
 // Tiles of a product's workgroup beside the sweep: one, so that a long K is dealt to many workgroups, but
@@ -1075,10 +1075,9 @@ int beside_tiles(const SplitParams& p, const LinearParams& l) {
 template <int G, int MB>
 hipError_t launch_beside(const SplitParams& p, const LinearParams& l, hipStream_t stream) {
   const int tiles = lin::takes_tiles(l) ? beside_tiles(p, l) : 0;
-  const int rows = l.glu ? lin::beside_rows_glu(MB) : lin::beside_rows(MB);
   const int per_group = tiles * lin::kTileRows;
   const int linear_groups =
-      ((tiles ? (l.N + per_group - 1) / per_group : lin::linear_blocks(l.N, rows)) + 7) / 8;
+      ((tiles ? (l.N + per_group - 1) / per_group : lin::linear_blocks(l.N, lin::beside_rows(MB))) + 7) / 8;
   const unsigned grid = 8u * ((unsigned)p.units_per_xcd + (unsigned)linear_groups);
   const hipError_t e = launch_rank(p, stream);
   if (e != hipSuccess) return e;
@@ -1094,7 +1093,7 @@ hipError_t launch_beside(const SplitParams& p, const LinearParams& l, hipStream_
 
 template <int G>
 hipError_t launch_beside_g(const SplitParams& p, const LinearParams& l, hipStream_t stream) {
-  switch (lin::rows_bucket(l.M)) {
+  switch (lin::takes_tiles(l) ? kTilesBucket : lin::rows_bucket(l.M)) {
     case 1: return launch_beside<G, 1>(p, l, stream);
     case 2: return launch_beside<G, 2>(p, l, stream);
     case 4: return launch_beside<G, 4>(p, l, stream);
@@ -1148,6 +1147,10 @@ hipError_t launch_decode_split(const SplitParams& p, int group, hipStream_t stre
 
 hipError_t launch_decode_split_beside(const SplitParams& p, int group, const LinearParams& l,
                                      hipStream_t stream) {
+  if (lin::takes_single_rows(l)) {
+    const hipError_t e = launch_decode_split(p, group, stream);
+    return e != hipSuccess ? e : launch_linear(l, stream);
+  }
   switch (group) {
     case 1: return launch_beside_g<1>(p, l, stream);
     case 2: return launch_beside_g<2>(p, l, stream);

@@ -202,7 +202,6 @@ inline int linear_blocks(int N, int R) { return (N + kRowsPerBlock * R - 1) / (k
 // R for the shared launch with the sweep, where the product's workgroups run at the sweep's
 // occupancy: more rows per wavefront keep enough weight bytes in flight.
 constexpr int beside_rows(int MB) { return MB <= 2 ? 4 : MB <= 4 ? 2 : 1; }
-constexpr int beside_rows_glu(int MB) { return MB <= 2 ? 4 : 2; }
 
 // U for a row length K: the chunks of K in one group where registers allow (at most 8 loads of weights
 // plus 8 of inputs per lane), else the group size in 4 .. 8 that leaves the fewest chunks past the end

@@ -110,12 +110,8 @@ __device__ __forceinline__ void linear_tiles(
   const int per = GLU ? n_rows / 2 : n_rows;
   const int om = (int)threadIdx.x / per, on = (GLU ? 2 : 1) * ((int)threadIdx.x % per);
   uint16_t res = 0;
-  if constexpr (!GLU) {
-    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(residual != nullptr ? residual + n0 : w), (short)0,
-        residual != nullptr ? (M * N - n0) * 2 : 0, 0x00020000);
-    res = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rr, (om * N + on) * 2, 0, 0);
-  }
+  if constexpr (!GLU)
+    if (residual != nullptr && om < M) res = residual[(size_t)om * N + n0 + on];
 
   struct Step {
     uint4 w[T], x, g;
@@ -299,11 +295,15 @@ __device__ __forceinline__ void linear_tiles(
   }
 }
 
-// Whether a product of M input rows, N outputs and K inputs takes the tiles: more than kVectorRows
-// rows (below, the vector path), a prologue that two bf16 halves carry exactly, and 32-bit offsets.
+// Whether a product takes the tiles: more than kVectorRows rows (below, the vector path), a prologue that
+// two bf16 halves carry exactly, and 32-bit offsets (40 rows of K weights).
 constexpr int kVectorRows = 1;
 inline bool takes_tiles(const LinearParams& p) {
-  return p.M > kVectorRows && p.prologue != kProSwiglu && p.K <= (1 << 20) && p.N <= (1 << 26);
+  return p.M > kVectorRows && p.prologue != kProSwiglu && p.K <= (1 << 24);
+}
+// Whether its rows are taken one by one, on the vector path: what is left of several rows without SwiGLU.
+inline bool takes_single_rows(const LinearParams& p) {
+  return p.M > kVectorRows && p.prologue != kProSwiglu && !takes_tiles(p);
 }
 
 }  // namespace lin

@@ -41,6 +41,7 @@ CASES = [  # (M, N, K, prologue, residual, split, GLU output)
     (3, 2600, 5128, None, False, None, False),
     (6, 1026, 2056, "rms_norm", False, None, True),       # 1 tile, two in flight: 3 rounds
     (8, 264, 9736, None, True, None, False),              # 10 rounds
+    (3, 9, (1 << 20) + 8, "rms_norm", True, 4, False),
     (2, 4201, 4168, None, False, None, False),            # beside a sweep: one tile, 526 workgroups
     (2, 4201, 4096, None, False, None, False),            # two tiles, 263
     (3, 1985, 520, "rms_norm", False, 1984, False),       # one tile, all on units of their own
@@ -89,6 +90,42 @@ def test_tiles_match_the_oracle_and_the_shared_launch(gpu, M, N, K, pro, res, sp
     out = got.double().cpu().numpy()
     ok = (out >= lo) & (out <= hi)
     assert ok.all(), (np.argwhere(~ok)[:4], out[~ok][:4], ref[~ok][:4])
+
+
+@pytest.mark.parametrize("pro,glu", [(None, False), ("rms_norm", True)])
+def test_rows_too_long_for_the_tiles_are_taken_one_by_one(gpu, pro, glu):
+    """K past the tiles' offsets (2^24): by themselves and beside a sweep, each row is bitwise the call
+    with that row alone, and the sum that torch gives in fp64."""
+    M, N, K = 3, 6, (1 << 24) + 8
+    gen = torch.Generator(device=gpu).manual_seed(77)
+    x = torch.randn(M, K, generator=gen, device=gpu).to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=gen, device=gpu) / 4096).to(torch.bfloat16)
+    g = torch.ones(K, device=gpu, dtype=torch.bfloat16) if pro else None
+    r = None if glu else torch.randn(M, N, generator=gen, device=gpu).to(torch.bfloat16)
+    say(f"[tiles] K={K} {pro} glu={glu}")
+    kw = dict(prologue=pro, gain=g, eps=1e-6, glu_out=glu)
+    cut = None if glu else 4
+    rows = [qf.linear(x[m:m + 1], w, residual=None if glu else r[m:m + 1], split=cut, **kw)
+            for m in range(M)]
+    got = qf.linear(x, w, residual=r, split=cut, **kw)
+    case = make_case(2, 4, 2, [300, 17], [2, 1], seed=3, device=gpu)
+    beside = qf.attn_decode_split_beside(case.q, case.k_cache, case.v_cache, case.block_table,
+                                         case.ctx_lens, case.n_shards,
+                                         dict(x=x, w=w, residual=r, split=cut, **kw), max_shards=2,
+                                         scale=case.scale)[2]
+    torch.cuda.synchronize()
+    got, beside = (torch.cat(t, 1) if cut else t for t in (got, beside))
+    want = torch.cat([torch.cat(t, 1) if cut else t for t in rows])
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert torch.equal(beside.view(torch.int16), want.view(torch.int16))
+    for m in range(M):
+        y = (w.double() * x[m].double()).sum(1)
+        if pro:
+            y = y / torch.sqrt((x[m].double() ** 2).mean() + 1e-6)
+        y = y[0::2] * torch.sigmoid(y[0::2]) * y[1::2] if glu else y + r[m].double()
+        # sums of 2^24 terms of size 2^-12: (K/64 + 32) 2^-24 of the absolute sum, 2^12 * 0.64, is 41;
+        # fp32 sums of random signs stay within a thousandth of it
+        torch.testing.assert_close(got[m].double(), y, rtol=2 ** -7, atol=0.05)
 
 
 @pytest.mark.parametrize("N,K,pro,glu", [(64, 512, None, False), (1024, 3072, None, False),
