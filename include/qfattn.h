@@ -199,9 +199,10 @@ int qf_attn_decode(const qf_decode_desc* desc, const void* q, const void* k_cach
  * qf_attn_decode for callers that cannot allocate device memory or pass a workspace (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same sweep and
  * merge, with the same results (bitwise) as qf_attn_decode on the same inputs, but the partial
- * states live in a fixed device array of the library's own, QF_NOALLOC_SCRATCH_BYTES (64 MiB) on every
- * GPU the library runs on, held until the process ends.  The call allocates nothing; it enqueues
- * two kernels, the sweep and the merge (there are no arrival counters to keep).
+ * states live in a fixed device array of the library's own, QF_NOALLOC_STATE_BYTES on every GPU the
+ * library runs on (never more than QF_NOALLOC_SCRATCH_BYTES, 64 MiB), held until the process ends.  The
+ * call allocates nothing; it enqueues two kernels, the sweep and the merge (there are no arrival counters
+ * to keep).
  *
  *   q ... n_shards, out, lse   as for qf_attn_decode.
  *   stream                     hipStream_t of the CURRENT device (the scratch used is the current

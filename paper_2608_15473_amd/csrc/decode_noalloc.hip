@@ -18,12 +18,12 @@
 #include "qf_internal.h"
 #include "qfattn.h"
 
-static_assert(QF_NOALLOC_SCRATCH_BYTES == qf::kNoallocScratchBytes, "scratch size of the header");
-static_assert(QF_NOALLOC_STATE_BYTES == qf::kNoallocStateBytes, "state bytes of the header");
-static_assert(QF_NOALLOC_MAX_GROUPS * sizeof(int32_t) == qf::kNoallocCounterBytes,
-              "counter count of the header");
+static_assert(QF_NOALLOC_STATE_BYTES == qf::kNoallocStateBytes &&
+                  QF_NOALLOC_STATE_BYTES <= QF_NOALLOC_SCRATCH_BYTES,
+              "state bytes of the header");
+static_assert(QF_NOALLOC_MAX_GROUPS == qf::kNoallocMaxGroups, "groups of the header");
 
-static __device__ __align__(256) unsigned char scratch[qf::kNoallocScratchBytes];
+static __device__ __align__(256) unsigned char scratch[qf::kNoallocStateBytes];
 
 namespace qf {
 namespace {
@@ -53,7 +53,7 @@ hipError_t noalloc_states(void** states) {
       g_scratch[dev].store(base, std::memory_order_release);
     }
   }
-  *states = base + kNoallocCounterBytes;
+  *states = base;
   return hipSuccess;
 }
 

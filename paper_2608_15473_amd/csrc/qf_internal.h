@@ -164,12 +164,11 @@ int simulate_schedule(int R, const double* arrival, const double* attn_time, int
 
 hipError_t launch_decode_split(const SplitParams& p, int group, hipStream_t stream);
 
-// The allocation-free decode's fixed scratch (decode_noalloc.hip): one device array per GPU of
-// kNoallocScratchBytes, the partial states after its first kNoallocCounterBytes (unused; they and the
-// bound on (request, KV head) groups that they stood for are part of the interface).
-constexpr size_t kNoallocScratchBytes = size_t(64) << 20;
-constexpr size_t kNoallocCounterBytes = size_t(256) << 10;
-constexpr size_t kNoallocStateBytes = kNoallocScratchBytes - kNoallocCounterBytes;
+// The allocation-free decode's fixed scratch (decode_noalloc.hip): one device array per GPU for the partial
+// states.  The sizes that a call may have are the interface's (the bound on (request, KV head) groups and
+// the 256 KiB below the 64 MiB date from a form with arrival counters in the array).
+constexpr size_t kNoallocStateBytes = (size_t(64) << 20) - (size_t(256) << 10);
+constexpr int64_t kNoallocMaxGroups = 65536;
 // This device's scratch (looked up on the first call on the device).
 hipError_t noalloc_states(void** states);
 

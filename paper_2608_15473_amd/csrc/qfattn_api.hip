@@ -442,25 +442,23 @@ int decode_fused(const qf_decode_desc* desc, const void* q, const void* k_cache,
   const int64_t groups = (int64_t)d.batch * d.n_kv_heads;
   if (fixed_scratch) {
     // Sizes first: a shape beyond the fixed scratch is refused before anything touches the GPU.
-    const int64_t max_groups = (int64_t)(qf::kNoallocCounterBytes / sizeof(int32_t));
-    if (need > qf::kNoallocStateBytes || groups > max_groups)
+    if (need > qf::kNoallocStateBytes || groups > qf::kNoallocMaxGroups)
       return fail(QF_EINVAL,
-                  "shape needs %zu bytes of partial states and %lld (request, KV head) counters; "
-                  "the fixed scratch holds %zu bytes and %lld counters (qf_attn_decode takes a "
+                  "shape needs %zu bytes of partial states and has %lld (request, KV head) groups; "
+                  "the fixed scratch takes %zu bytes and %lld groups (qf_attn_decode takes a "
                   "workspace of any size)",
-                  need, (long long)groups, qf::kNoallocStateBytes, (long long)max_groups);
-    // Placeholders (aligned, never dereferenced) until the arguments have been checked.
+                  need, (long long)groups, qf::kNoallocStateBytes, (long long)qf::kNoallocMaxGroups);
+    if (!out) return fail(QF_EINVAL, "out is required");
+    // A placeholder (aligned, never dereferenced) until the arguments have been checked.
     workspace = reinterpret_cast<void*>(uintptr_t(256));
     workspace_size = need;
-    counters = reinterpret_cast<int32_t*>(uintptr_t(256));  // not used
-    n_counters = groups;
-    if (!out) return fail(QF_EINVAL, "out is required");
-  } else if (!out || !workspace || !counters) {
-    return fail(QF_EINVAL, "out, workspace and counters are required");
+  } else {
+    if (!out || !workspace || !counters)
+      return fail(QF_EINVAL, "out, workspace and counters are required");
+    if (n_counters < groups)
+      return fail(QF_EINVAL, "counters holds %lld entries < batch * n_kv_heads = %lld",
+                  (long long)n_counters, (long long)groups);
   }
-  if (n_counters < groups)
-    return fail(QF_EINVAL, "counters holds %lld entries < batch * n_kv_heads = %lld",
-                (long long)n_counters, (long long)groups);
   if (!aligned(out, 4) || (lse && !aligned(lse, 4)) || !aligned(workspace, 16) ||
       !aligned(counters, 4))
     return fail(QF_EALIGN, "out, lse and counters must be 4-byte aligned, workspace 16-byte");

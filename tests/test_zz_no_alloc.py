@@ -31,7 +31,7 @@ def _desc(**kw):
 @pytest.mark.parametrize("kw", [
     dict(batch=4096, n_q_heads=64, n_kv_heads=8, max_shards=64, max_pages_per_seq=4096,
          num_pages=1 << 20),                                  # partial states beyond the array
-    dict(batch=10000, n_q_heads=8, n_kv_heads=8, max_shards=1, num_pages=1 << 21),  # counters
+    dict(batch=10000, n_q_heads=8, n_kv_heads=8, max_shards=1, num_pages=1 << 21),  # groups
 ])
 def test_shapes_beyond_the_scratch_are_refused_on_the_host(kw):
     lib = load_library()
