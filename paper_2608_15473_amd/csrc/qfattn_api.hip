@@ -92,9 +92,10 @@ bool long_shards(const qf_decode_desc* d, int64_t chunks) {
 //    4): an eighth of a request's slots, so that they are spread over the 8 XCDs and each XCD still meets
 //    few block-table lines and queries (their first read on an XCD is a miss that a short workgroup cannot
 //    hide: with single slots dealt round, one request of 5,049 positions at 2 KV heads took 13.9 us a layer
-//    instead of 12.7, and 16 requests of 32,768 positions at G = 8 370 instead of 365).  A request of few
-//    units (kDealFewUnits: one per compute unit) takes them whether even or not, since none waits for
-//    another: 1,721 positions at 26 shards, 2 KV heads 8.9 -> 7.6 us.
+//    instead of 12.7, and 16 requests of 32,768 positions at G = 8 370 instead of 365).  One request of few
+//    units (kDealFewUnits: one per compute unit) may leave an XCD out, since no unit waits for another
+//    (1,721 positions at 26 shards, 2 KV heads 8.9 -> 7.6 us, contiguous units 8.0); where more would be
+//    left out, or more units uneven, each XCD takes an eighth of its units.
 //  * Fewer units of several requests: slots of kDealItemUnits units, since their lengths may differ and a
 //    few long requests' slots must not meet on one XCD (12 requests of 27 to 7,003 positions, 8 KV heads,
 //    28.3 -> 27.5 us a layer, 7 of 10 to 2,723 at 42 shards 24.6 -> 22.6; batches of one length lose 0-0.5%).
@@ -108,9 +109,13 @@ int32_t units_per_item(const qf_decode_desc* d, int64_t chunks) {
   const int64_t slots = (int64_t)d->max_shards * chunks, all = slots * d->batch;
   const int64_t units = all * d->n_kv_heads, hkv = d->n_kv_heads;
   if (units > qf::kDealMostUnits) return (int32_t)((units + 7) / 8);
-  const bool local = d->batch == 1 || units >= qf::kDealManyUnits;
-  int64_t k = local ? (slots + 7) / 8 : (qf::kDealItemUnits + hkv - 1) / hkv;
-  if (d->batch == 1 && units <= qf::kDealFewUnits) return (int32_t)(k * hkv);
+  const int64_t eighth = (slots + 7) / 8;
+  if (d->batch == 1) {
+    const int64_t items = (slots + eighth - 1) / eighth;
+    const bool even = (items + 7) / 8 * eighth * 64 <= slots * 9;
+    return (int32_t)((units <= qf::kDealFewUnits ? items >= 7 : even) ? eighth * hkv : (units + 7) / 8);
+  }
+  int64_t k = units >= qf::kDealManyUnits ? eighth : (qf::kDealItemUnits + hkv - 1) / hkv;
   for (; k > 0; --k)
     if (((all + k - 1) / k + 7) / 8 * k * 64 <= all * 9) return (int32_t)(k * hkv);
   return 1;

@@ -27,25 +27,29 @@ MANY, FEW, ITEM, DEEP_MANY = (int(CONST[k]) for k in ("kDealManyUnits", "kDealFe
                                                       "kDealItemUnits", "kDeepManyUnits"))
 
 
-def _slots_per_item(batch, slots, hkv):
-    """The rule between the item sizes, restated (0: single units)."""
-    n, units = batch * slots, batch * slots * hkv
-    k = -(-slots // 8) if batch == 1 or units >= MANY else -(-ITEM // hkv)
-    if batch == 1 and units <= FEW:
-        return k
-    while k and -(-(-(-n // k)) // 8) * k * 64 > n * 9:
+def _units_per_item(batch, slots, hkv):
+    """The rule between the item sizes, restated."""
+    n, units, k = batch * slots, batch * slots * hkv, -(-slots // 8)
+    even = lambda k: -(-(-(-n // k)) // 8) * k * 64 <= n * 9
+    if batch == 1:
+        good = -(-slots // k) >= 7 if units <= FEW else even(k)
+        return k * hkv if good else -(-units // 8)
+    if units < MANY:
+        k = -(-ITEM // hkv)
+    while k and not even(k):
         k -= 1
-    return k
+    return max(1, k * hkv)
 
 
 @pytest.mark.parametrize("batch,shards,hkv,G,item", [
-    (1, 1, 1, 1, 1), (1, 7, 3, 2, 1), (3, 3, 2, 4, 0), (9, 7, 3, 1, 2), (8, 8, 5, 1, 2), (5, 13, 3, 2, 3),
-    (13, 9, 7, 2, 2), (72, 1, 11, 1, 1),
-    (1, 65, 3, 1, 9), (1, 26, 2, 1, 4),       # few units of one request: an eighth, the last item short
-    (1, 300, 8, 2, 38), (1, 43, 7, 4, 6),     # more: an eighth where even
-    (1, 42, 7, 1, 0),                         # and where no number of slots is
-    (7, 13, 1, 2, 6), (11, 9, 2, 1, 1),       # several requests, few KV heads
-    (23, 29, 7, 1, 4),                        # many units of several requests, 167 items
+    (1, 1, 1, 1, 1), (1, 7, 3, 2, 3), (3, 3, 2, 4, 1), (9, 7, 3, 1, 6), (8, 8, 5, 1, 10), (5, 13, 3, 2, 9),
+    (13, 9, 7, 2, 14), (72, 1, 11, 1, 11),
+    (1, 65, 3, 1, 27), (1, 26, 2, 1, 8),      # few units of one request: an eighth of the slots, the last item short
+    (1, 4, 24, 1, 12), (1, 9, 5, 2, 6),       # or of the units, slots cut
+    (1, 300, 8, 2, 304), (1, 43, 7, 4, 42),   # more: of the slots where even,
+    (1, 42, 7, 1, 37),                        # of the units where not
+    (7, 13, 1, 2, 6), (11, 9, 2, 1, 2),       # several requests, few KV heads
+    (23, 29, 7, 1, 28),                       # many units of several requests, 167 items
 ])
 def test_every_unit_is_swept_once(gpu, batch, shards, hkv, G, item):
     rng = np.random.default_rng(1000 * batch + shards)
@@ -54,8 +58,8 @@ def test_every_unit_is_swept_once(gpu, batch, shards, hkv, G, item):
     case = make_case(batch, G * hkv, hkv, ctx, np.minimum(shards, 1 + ctx // 16), seed=900 + batch,
                      max_shards=shards, device=gpu)
     chunks = qf.split_chunks(qf.make_desc(case.q, case.k_cache, case.block_table, shards, case.scale))
-    assert _slots_per_item(batch, shards * chunks, hkv) == item
-    say(f"[deal] batch {batch}, {shards} shards, {hkv} KV heads, G {G}, items of {item} slots")
+    assert _units_per_item(batch, shards * chunks, hkv) == item
+    say(f"[deal] batch {batch}, {shards} shards, {hkv} KV heads, G {G}, items of {item} units")
     got = run_gpu(case)
     check(case, got, oracle_ref(case), label="deal")
     out, lse = qf.attn_decode(case.q, case.k_cache, case.v_cache, case.block_table, case.ctx_lens,
