@@ -979,7 +979,7 @@ sweep_beside_linear_kernel(
     const uint16_t* __restrict__ w,
     const uint16_t* __restrict__ gain, const uint16_t* __restrict__ residual,
     uint16_t* __restrict__ out_a, uint16_t* __restrict__ out_b, int32_t M, int32_t N, int32_t K,
-    int32_t n_split, float eps, int32_t prologue, int32_t glu, int32_t tiles,
+    int32_t n_split, float eps, int32_t prologue, int32_t glu, int32_t tiles /* one row: rows a wavefront */,
     int32_t linear_groups) {
   static_assert(64 * kSplitWaves == lin::kThreads, "both roles use the same workgroup size");
   const unsigned j = blockIdx.x / 8u, lane8 = blockIdx.x % 8u;
@@ -1026,32 +1026,36 @@ sweep_beside_linear_kernel(
     else
       tile(std::integral_constant<int, 2>{});
   } else if constexpr (MB == 1) {
-    // K in groups of three chunks of 512 from 1,024 to 10,240 inputs, else of two.  Fewer waits are worth
-    // the loads past the end that three may add: one row beside the sweep of one request of 4,608
-    // positions, us with groups of two and three: 1,024 x 2,048 7.43 / 7.35, 2,048 x 2,560 9.62 / 9.22,
-    // 1,024 x 3,072 8.05 / 7.41, 2,560 x 4,096 11.6 / 11.2, 2,560 x 9,728 20.4 / 17.9, but 4,096 x 14,336
+    // K in groups of three chunks of 512 from 1,024 to 10,240 inputs, else of two (with two rows a wavefront
+    // always three).  Fewer waits are worth the loads past the end that three may add: one row beside the
+    // sweep of one request of 4,608 positions, us with groups of two and three: 1,024 x 2,048 7.43 / 7.35,
+    // 2,048 x 2,560 9.62 / 9.22, 1,024 x 3,072 8.05 / 7.41, 2,560 x 4,096 11.6 / 11.2, but 4,096 x 14,336
     // 29.7 / 30.2, where many groups hide a wait.
-    auto rows = [&](auto unroll) {
-      constexpr int U = decltype(unroll)::value;
-      if (glu) {
-        if (prologue == kProRmsNorm)
-          lin::linear_rows<kProRmsNorm, 1, U, R, true>(x, w, gain, residual, out_a, out_b, M, N, K, n_split,
-                                                       eps, lb);
-        else
-          lin::linear_rows<kProNone, 1, U, R, true>(x, w, gain, residual, out_a, out_b, M, N, K, n_split,
-                                                    eps, lb);
-      } else if (prologue == kProRmsNorm) {
-        lin::linear_rows<kProRmsNorm, 1, U, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
-      } else if (prologue == kProSwiglu) {
-        lin::linear_rows<kProSwiglu, 1, U, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
-      } else {
-        lin::linear_rows<kProNone, 1, U, R>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
-      }
+    auto rows = [&](auto unroll, auto per) {
+      constexpr int U = decltype(unroll)::value, RW = decltype(per)::value;
+      if (prologue == kProRmsNorm)
+        lin::linear_rows<kProRmsNorm, 1, U, RW>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
+      else if (prologue == kProSwiglu)
+        lin::linear_rows<kProSwiglu, 1, U, RW>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
+      else
+        lin::linear_rows<kProNone, 1, U, RW>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps, lb);
     };
-    if (K > 1024 && K <= 10240)
-      rows(std::integral_constant<int, 3>{});
-    else
-      rows(std::integral_constant<int, 2>{});
+    auto gated = [&](auto unroll) {
+      constexpr int U = decltype(unroll)::value;
+      if (prologue == kProRmsNorm)
+        lin::linear_rows<kProRmsNorm, 1, U, R, true>(x, w, gain, residual, out_a, out_b, M, N, K, n_split,
+                                                     eps, lb);
+      else
+        lin::linear_rows<kProNone, 1, U, R, true>(x, w, gain, residual, out_a, out_b, M, N, K, n_split, eps,
+                                                  lb);
+    };
+    using std::integral_constant;
+    const bool three = K > 1024 && K <= 10240;
+    if (glu && three) gated(integral_constant<int, 3>{});
+    else if (glu) gated(integral_constant<int, 2>{});
+    else if (tiles == 2) rows(integral_constant<int, 3>{}, integral_constant<int, 2>{});
+    else if (three) rows(integral_constant<int, 3>{}, integral_constant<int, R>{});
+    else rows(integral_constant<int, 2>{}, integral_constant<int, R>{});
   }
 }
 
@@ -1072,12 +1076,22 @@ int beside_tiles(const SplitParams& p, const LinearParams& l) {
   return rounds || own ? 2 : 1;
 }
 
+// Whether one row's product beside the sweep has two output rows a wavefront, not beside_rows: a long K is
+// then dealt to twice the wavefronts (us, four and two: 2,048 x 5,632 13.5 / 11.6, 2,560 x 9,728 18.4 /
+// 16.2, 4,096 x 11,008 26.3 / 22.9, beside 32 KV heads 44.4 / 34.0).  A short one is better in few
+// workgroups (1,024 x 3,072 7.8 / 9.3, 6,144 x 1,024 with GLU 9.2 / 10.6), a very long one keeps enough
+// loads in flight with four (5,120 x 25,600 52.3 / 59.3).
+bool beside_two_rows(const LinearParams& l) {
+  return l.M == 1 && !l.glu && l.N >= 2048 && l.K > 4096 && l.K <= 16384;
+}
+
 template <int G, int MB>
 hipError_t launch_beside(const SplitParams& p, const LinearParams& l, hipStream_t stream) {
-  const int tiles = lin::takes_tiles(l) ? beside_tiles(p, l) : 0;
-  const int per_group = tiles * lin::kTileRows;
-  const int linear_groups =
-      ((tiles ? (l.N + per_group - 1) / per_group : lin::linear_blocks(l.N, lin::beside_rows(MB))) + 7) / 8;
+  const bool two = MB == 1 && beside_two_rows(l);
+  const int tiles = lin::takes_tiles(l) ? beside_tiles(p, l) : two ? 2 : 0;
+  const int per_group = lin::takes_tiles(l) ? tiles * lin::kTileRows
+                                            : lin::kRowsPerBlock * (two ? 2 : lin::beside_rows(MB));
+  const int linear_groups = ((l.N + per_group - 1) / per_group + 7) / 8;
   const unsigned grid = 8u * ((unsigned)p.units_per_xcd + (unsigned)linear_groups);
   const hipError_t e = launch_rank(p, stream);
   if (e != hipSuccess) return e;

@@ -145,14 +145,22 @@ def test_a_row_has_the_same_bits_among_any_others(gpu, N, K, pro, glu):
             assert torch.equal(got, full[at:at + m]), (m, at)
 
 
-@pytest.mark.parametrize("K", [1016, 1024, 1032, 1536, 2048, 2560, 10240, 10248, 11776])
-@pytest.mark.parametrize("pro,glu", [(None, False), ("rms_norm", True)])
-def test_one_row_beside_a_sweep_equals_the_call_bitwise(gpu, K, pro, glu):
-    """The groups of chunks of a single row's K in the shared launch (two or three, whole or not)."""
-    x, w, g, r = _inputs(gpu, 1, 78, K, pro, not glu)
+@pytest.mark.parametrize("N,K", [(78, k) for k in (1016, 1024, 1032, 1536, 2048, 2560, 10240, 10248, 11776)]
+                         + [(2046, 4104), (2050, 4096), (2051, 4104), (2048, 4608), (2050, 11784),
+                            (2050, 16384), (2050, 16392)])
+@pytest.mark.parametrize("pro,glu", [(None, False), ("rms_norm", False), ("rms_norm", True),
+                                     ("swiglu", False)])
+def test_one_row_beside_a_sweep_equals_the_call_bitwise(gpu, N, K, pro, glu):
+    """The groups of chunks of a single row's K in the shared launch (two or three, whole or not), with
+    four output rows a wavefront and with two."""
+    if glu and N % 2:
+        N += 1
+    x, w, g, r = _inputs(gpu, 1, N, K, pro == "rms_norm", not glu)
+    if pro == "swiglu":
+        x = torch.cat([x, x.flip(1)], 1).contiguous()
     kw = dict(x=x, w=w, prologue=pro, gain=g, residual=r, glu_out=glu)
     case = make_case(2, 4, 2, [300, 17], [2, 1], seed=3, device=gpu)
-    say(f"[tiles] one row beside a sweep, K={K} {pro} glu={glu}")
+    say(f"[tiles] one row beside a sweep, N={N} K={K} {pro} glu={glu}")
     got = qf.attn_decode_split_beside(case.q, case.k_cache, case.v_cache, case.block_table,
                                       case.ctx_lens, case.n_shards, kw, max_shards=2,
                                       scale=case.scale)[2]
