@@ -22,7 +22,11 @@ the two may run at once.  On one GPU this module offers three orders of the same
 
 For one request, where every launch is latency, the merge of the shards runs beside W_k|W_v N1(z)
 (qf_linear_beside_merge) and the current-token fold and the append in W_o's launch
-(qf_linear_attn_current), in all three modes: four launches a block in "fused".
+(qf_linear_attn_current), in all three modes: four launches a block in "fused".  Every workgroup of that
+launch folds all heads, so with many of them it takes longer than the launch it saves: measured on blocks
+at 400 and 4,608 positions (us a block with five launches and with four, "fused"), 16 heads 1,024 wide
+26.1 -> 22.6, 32 heads 4,096 wide 90.4 -> 83.9, 64 heads 1,024 wide 33.8 -> 33.2, but 64 heads 5,120 wide
+169.6 -> 170.5, 96 heads 91.6 -> 93.0 and 128 heads 101.5 -> 108.7.
 
 Every step is one of the library's HIP kernels: the four products fused with the normalisation
 or activation that feeds them and the residual add that follows (qf_linear), the sweep, and the merge
@@ -107,7 +111,9 @@ class QFirstStack:
         self.lse = buf(B, self.hq, dtype=torch.float32)
         self.part_out = buf(B, self.max_shards, self.hq, D, dtype=torch.float32)
         self.part_lse = buf(B, self.max_shards, self.hq, dtype=torch.float32)
-        if B == 1:                                            # the merged pair of the cache
+        # One request of few heads: the short tail of a block (the module's comment has the figures).
+        self.short_tail = B == 1 and (self.hq <= 32 or self.hq <= 64 and H <= 2048)
+        if self.short_tail:                                   # the merged pair of the cache
             self.merged = buf(B, self.hq, D, dtype=torch.float32)
             self.merged_lse = buf(B, self.hq, dtype=torch.float32)
         self.status = torch.zeros(1, dtype=torch.int32, device=self.device)
@@ -175,8 +181,7 @@ class QFirstStack:
                 self._linear(u, w["w_gu"], self.act, "rms_norm", w["g2"], glu_out=True)
             with self._span("W_down"):                                       # z = u + M(N2 u)
                 self._linear(self.act, w["w_down"], self.z, residual=u)
-        if B == 1:
-            # one request: the tail of the block in two launches, in every mode
+        if self.short_tail:                                   # two launches, in every mode
             if mode == "streams":
                 main.wait_stream(self.attn_stream)
             with self._span("W_k,W_v + merge"):                              # k, v read z

@@ -15,7 +15,7 @@ import torch
 import paper_2608_15473_amd as qf
 from parity import say
 from test_gpu_stage import SHAPE, _build, _restore, _same_state, _state
-from workloads import make_case
+from workloads import BlockShape, make_case
 
 pytestmark = pytest.mark.gpu
 
@@ -94,9 +94,13 @@ def test_a_full_cache_and_two_requests_are_refused(gpu):
     assert e.value.code == qf.QF_EUNSUPPORTED
 
 
-@pytest.mark.parametrize("ctx,shards", [(300, 3), (0, 1), (2, 2)])
-def test_stack_of_one_request_in_all_modes(gpu, ctx, shards):
-    stack, u = _build(gpu, seed=810, ctx=np.array([ctx]), shards=[shards])
+MANY = BlockShape("many heads", hidden=256, inter=512, n_q_heads=72, n_kv_heads=9, layers=3)
+
+
+@pytest.mark.parametrize("ctx,shards,shape", [(300, 3, SHAPE), (0, 1, SHAPE), (2, 2, SHAPE), (77, 2, MANY)])
+def test_stack_of_one_request_in_all_modes(gpu, ctx, shards, shape):
+    stack, u = _build(gpu, seed=810, ctx=np.array([ctx]), shards=[shards], shape=shape)
+    assert stack.short_tail == (shape is SHAPE)
     saved = _state(stack)
     ys, states = {}, {}
     for mode in ("serial", "streams", "fused"):
@@ -122,4 +126,4 @@ def test_stack_of_one_request_in_all_modes(gpu, ctx, shards):
         assert torch.equal(out, ys["serial"][0]), r
         stack.step(u, mode="serial")
         torch.cuda.synchronize()
-    assert SHAPE.layers == len(stack.layers)
+    assert shape.layers == len(stack.layers)
