@@ -74,7 +74,8 @@ def committed_traffic(workload, two_launch=True):
     return rec["traffic_bytes_per_launch"]
 
 
-KERNEL_SOURCES = ("decode_split.hip", "merge.hip", "linear_body.h", "merge_body.h", "qf_internal.h")
+KERNEL_SOURCES = ("decode_split.hip", "merge.hip", "linear_body.h", "linear_mfma.h", "merge_body.h",
+                  "qf_internal.h")
 
 
 def kernel_source_digest():
@@ -471,7 +472,7 @@ def main():
     lse = torch.empty((B, Hq), dtype=torch.float32, device=dev)
     need = qf.decode_workspace_size(desc) if args.one_launch else 0
     ws = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
-    counters = torch.zeros(B * Hkv, dtype=torch.int32, device=dev)  # zero-filled once
+    counters = torch.zeros(32 * B * Hkv, dtype=torch.int32, device=dev)  # zero-filled once
 
     turn = [0]
     # The two-launch step of each resident copy, checked and converted once (the host then does

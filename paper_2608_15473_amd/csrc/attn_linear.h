@@ -2,8 +2,8 @@
 // it (Q-First, arXiv:2608.15473, §2): at one request every launch of a block costs 3 to 5 us of latency
 // against 1 us of bytes, so the number of launches is what bounds a step.
 //
-//  * merge_beside_rows: the merge of the shard slots into one (O, ln Z) per query head beside a product
-//    (W_k|W_v N1(z)): neither reads what the other writes.
+//  * linear_merge_kernel (block_ops.hip): the merge of the shard slots into one (O, ln Z) per query head
+//    beside a product (W_k|W_v N1(z)): neither reads what the other writes.
 //  * attn_rows: out = W . attn (+ residual) where attn is the current token folded into that pair
 //    (merge_body.h), computed by every workgroup for itself into LDS: 16 lanes hold one head, 8 dims
 //    each, so the score of the current token is a 16-lane reduction.  The weights are requested first.
@@ -25,7 +25,7 @@ namespace lin {
 
 // Merged attention of one request's cached positions and its current token (device pointers).
 struct AttnFold {
-  const float* o;          // fp32 [Hq, D], not read where lse is -inf
+  const float* o;          // fp32 [Hq, D]; where lse is -inf it may hold anything: selected out
   const float* lse;        // fp32 [Hq]
   const uint16_t* q;       // bf16 [Hq, D]
   const uint16_t* k_cur;   // bf16 [Hkv, D]

@@ -21,7 +21,7 @@
 //
 // Sums.  K is dealt in blocks of 64 inputs to 16 slots, a round of 1,024 inputs after the other; each
 // slot's sum is one chain of matrix instructions, and the slots' sums meet in one fixed tree.  A
-// workgroup of W wavefronts keeps 16 / W slots in each: T, W, the rows of a workgroup and the rounds
+// workgroup of W = 4 or 8 wavefronts keeps 16 / W slots in each: T, W, the rows of a workgroup and the rounds
 // in flight change nothing in any sum, so every launch of a product gives the same bits.
 //
 // With the RMS prologue the factor x * gain has up to 16 significant bits, so it is fed exactly as two
@@ -75,7 +75,7 @@ __device__ __attribute__((noinline)) inline float plain_sum(const uint16_t* x, c
 }
 
 // Output rows n0 .. n0 + rows - 1 (rows <= 8 T, even with GLU) of out = W . P(x) (+ residual),
-// M <= 8 input rows, by a workgroup of W (4, 8 or 16) wavefronts with the loads of RB rounds in
+// M <= 8 input rows, by a workgroup of W (4 or 8) wavefronts with the loads of RB rounds in
 // flight.  lds: one per workgroup.
 template <int PRO, int T, int W, int RB, bool GLU>
 __device__ __forceinline__ void linear_tiles(
@@ -84,7 +84,7 @@ __device__ __forceinline__ void linear_tiles(
     uint16_t* __restrict__ out_a, uint16_t* __restrict__ out_b, int32_t M, int32_t N, int32_t K,
     int32_t n_split, float eps, const int32_t n0, const int32_t rows, TileLds<T, W>& lds) {
   static_assert(PRO == kProNone || PRO == kProRmsNorm, "the SwiGLU input has 24 significant bits");
-  static_assert(W == 4 || W == 8 || W == 16, "whole slots per wavefront");
+  static_assert(W == 4 || W == 8, "the tree of the slots");
   constexpr int R = kTileRows;
   constexpr bool RMS = PRO == kProRmsNorm;
   constexpr int A = kSlots / W;                  // slots (steps per round) of a wavefront
@@ -170,7 +170,7 @@ __device__ __forceinline__ void linear_tiles(
   // moves no data but takes the compute unit's address path 16 cycles like any other, so none is
   // issued to keep the loop simple: the last RB rounds are computed after it, by the copy of the
   // code that starts at the right buffer.  (With such loads a product of 6,144 x 1,024 took 9.0 us for
-  // 8 rows instead of 6.1.)
+  // 8 rows instead of 6.1, then with 16 wavefronts a workgroup.)
   const int whole = K / kRoundK;
   const int rounds = whole + (whole * kRoundK < K ? 1 : 0);
   auto round_at = [&](int i) { return rounds > whole ? (i == 0 ? whole : i - 1) : i; };
@@ -257,8 +257,7 @@ __device__ __forceinline__ void linear_tiles(
   // Slot v's share of a sum over the workgroup's wavefronts.
   auto over_waves = [&](int v, auto&& at) {
     if constexpr (W == 4) return at(v);
-    else if constexpr (W == 8) return at(v) + at(v + 4);
-    else return (at(v) + at(v + 8)) + (at(v + 4) + at(v + 12));
+    else return at(v) + at(v + 4);
   };
   float scale = 1.0f;
   if constexpr (RMS) {

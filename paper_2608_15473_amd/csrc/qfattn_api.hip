@@ -29,15 +29,15 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 // second round (measured on the 1M-token shape, 128 units: 6 chunks beat 16 and 12).  The count
 // depends on the descriptor and the device's occupancy for the kernel only, so a given shape on a
 // given GPU always runs the same decomposition (and gives the same bits); with no device to ask
-// (a host without a GPU sizing a workspace) it assumes the counts this build reaches on an MI355X
-// (256 CUs; 4 workgroups per CU at G = 1, 3 at G = 2 and 4, 2 at G = 8), which a GPU test checks
-// against the device.
+// (a host without a GPU sizing a workspace) it assumes the counts that split_resident_workgroups gives on
+// an MI355X (256 CUs; 4 workgroups per CU at G = 1, 3 at G = 2 and 4, 2 at G = 8, no more than the kernel's
+// registers leave there), which a GPU test checks against the device.
 int64_t fallback_resident(int group) {
   return group == 1 ? 1024 : group == 8 ? 512 : 768;
 }
-// ... and no more chunks than leave every wavefront at least this many pages: on the 4,608-position
-// single layer (36 pages per shard) 3 pages per wavefront (3 chunks) beat 2 (4 chunks) by 2%,
-// 1 (9 chunks) by 17%, and 4 (2 chunks) by 6%.
+// ... and no more chunks than leave every wavefront at least this many pages: one layer of one request of
+// 4,608 positions (36 pages per shard), sweep and merge, took 9.80 us with 3 pages per wavefront (3 chunks),
+// 10.22 with 2 (4 chunks) and 10.45 with 4 (2 chunks) at G = 2, and 3 was the best at every group size.
 constexpr int64_t kMinPagesPerWave = 3;
 
 int check_desc(const qf_decode_desc* d) {
