@@ -32,6 +32,7 @@ constexpr int kLongShardPages = 128;
 constexpr int kDealManyUnits = 4096;
 constexpr int kDealFewUnits = 256;
 constexpr int kDealItemUnits = 8;
+constexpr int kDealMostSlots = 1024;
 constexpr int kDealMostUnits = 1 << 23;
 // Relative page shares of the sub-shard chunks of a long shard that run on even- and odd-numbered
 // XCDs (decode_split.hip): the odd XCDs stream slower.

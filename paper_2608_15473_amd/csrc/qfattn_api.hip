@@ -101,10 +101,14 @@ bool long_shards(const qf_decode_desc* d, int64_t chunks) {
 //    28.3 -> 27.5 us a layer, 7 of 10 to 2,723 at 42 shards 24.6 -> 22.6; batches of one length lose 0-0.5%).
 //    Single slots of few KV heads would share lines of the table and of the slots' log-sum-exps among the
 //    XCDs: 40 requests of 1,500 positions at 16 shards, 2 KV heads of one query head 18.7 -> 16.9 us, 30 of
-//    5,000 at 40, one KV head 21.1 -> 19.3; ragged ones of up to 7,000 positions within 2%.
-// Fewer slots where an XCD would get over an eighth more than the mean; single units where single slots
-// still do.  Above kDealMostUnits one contiguous range per XCD, which pads the grid by no workgroup: a
-// launch takes 2^24 - 1 of them, and 6,223 requests of 337 shards at 8 KV heads are 2^24 - 8.
+//    5,000 at 40, one KV head 21.1 -> 19.3; ragged ones of up to 7,000 positions within 2%.  As above, few
+//    units take them even or not (3 requests of 1,317 positions at 27 shards, 2 KV heads, in single slots 9.4
+//    us, contiguous 8.0).
+// Of those, the most slots that load no XCD over 1/32 more than the evenest number does (10 requests of
+// 7,926 positions, 5 KV heads, 20 slots each: two slots an item put 26 on an XCD and took 44.5 us, single
+// ones 25 and 41.9); single units where all load one over an eighth more than the mean.  Above
+// kDealMostUnits one contiguous range per XCD, which pads the grid by no workgroup: a launch takes 2^24 - 1
+// of them, and 6,223 requests of 337 shards at 8 KV heads are 2^24 - 8.
 int32_t units_per_item(const qf_decode_desc* d, int64_t chunks) {
   const int64_t slots = (int64_t)d->max_shards * chunks, all = slots * d->batch;
   const int64_t units = all * d->n_kv_heads, hkv = d->n_kv_heads;
@@ -115,10 +119,16 @@ int32_t units_per_item(const qf_decode_desc* d, int64_t chunks) {
     const bool even = (items + 7) / 8 * eighth * 64 <= slots * 9;
     return (int32_t)((units <= qf::kDealFewUnits ? items >= 7 : even) ? eighth * hkv : (units + 7) / 8);
   }
-  int64_t k = units >= qf::kDealManyUnits ? eighth : (qf::kDealItemUnits + hkv - 1) / hkv;
-  for (; k > 0; --k)
-    if (((all + k - 1) / k + 7) / 8 * k * 64 <= all * 9) return (int32_t)(k * hkv);
-  return 1;
+  const int64_t most = std::min<int64_t>(
+      units >= qf::kDealManyUnits ? eighth : (qf::kDealItemUnits + hkv - 1) / hkv, qf::kDealMostSlots);
+  if (units <= qf::kDealFewUnits && (all + most - 1) / most >= 8) return (int32_t)(most * hkv);
+  auto load = [&](int64_t k) { return ((all + k - 1) / k + 7) / 8 * k; };   // of the fullest XCD, in slots
+  int64_t least = load(1);
+  for (int64_t k = 2; k <= most; ++k) least = std::min(least, load(k));
+  if (least * 64 > all * 9) return 1;
+  int64_t k = most;
+  while (load(k) * 32 > least * 33) --k;
+  return (int32_t)(k * hkv);
 }
 
 // The deal of p's units in items of `run` (0: the long-shard order).

@@ -30,25 +30,29 @@ MANY, FEW, ITEM, DEEP_MANY = (int(CONST[k]) for k in ("kDealManyUnits", "kDealFe
 def _units_per_item(batch, slots, hkv):
     """The rule between the item sizes, restated."""
     n, units, k = batch * slots, batch * slots * hkv, -(-slots // 8)
-    even = lambda k: -(-(-(-n // k)) // 8) * k * 64 <= n * 9
+    load = lambda k: -(-(-(-n // k)) // 8) * k
     if batch == 1:
-        good = -(-slots // k) >= 7 if units <= FEW else even(k)
+        good = -(-slots // k) >= 7 if units <= FEW else load(k) * 64 <= n * 9
         return k * hkv if good else -(-units // 8)
     if units < MANY:
         k = -(-ITEM // hkv)
-    while k and not even(k):
-        k -= 1
-    return max(1, k * hkv)
+    if units <= FEW and -(-n // k) >= 8:
+        return k * hkv
+    least = min(load(i) for i in range(1, k + 1))
+    if least * 64 > n * 9:
+        return 1
+    return max(i for i in range(1, k + 1) if load(i) * 32 <= least * 33) * hkv
 
 
 @pytest.mark.parametrize("batch,shards,hkv,G,item", [
-    (1, 1, 1, 1, 1), (1, 7, 3, 2, 3), (3, 3, 2, 4, 1), (9, 7, 3, 1, 6), (8, 8, 5, 1, 10), (5, 13, 3, 2, 9),
-    (13, 9, 7, 2, 14), (72, 1, 11, 1, 11),
+    (1, 1, 1, 1, 1), (1, 7, 3, 2, 3), (3, 3, 2, 4, 1), (9, 7, 3, 1, 9), (8, 8, 5, 1, 10), (5, 13, 3, 2, 9),
+    (13, 9, 7, 2, 7), (72, 1, 11, 1, 11),
     (1, 65, 3, 1, 27), (1, 26, 2, 1, 8),      # few units of one request: an eighth of the slots, the last item short
     (1, 4, 24, 1, 12), (1, 9, 5, 2, 6),       # or of the units, slots cut
     (1, 300, 8, 2, 304), (1, 43, 7, 4, 42),   # more: of the slots where even,
     (1, 42, 7, 1, 37),                        # of the units where not
-    (7, 13, 1, 2, 6), (11, 9, 2, 1, 2),       # several requests, few KV heads
+    (7, 13, 1, 2, 8), (3, 27, 2, 1, 8),       # few units of several requests: of eight, the last item short
+    (10, 20, 5, 1, 5), (24, 17, 1, 2, 4),     # more: fewer slots where eight are less even
     (23, 29, 7, 1, 28),                       # many units of several requests, 167 items
 ])
 def test_every_unit_is_swept_once(gpu, batch, shards, hkv, G, item):
