@@ -516,9 +516,11 @@ int decode_fused(const qf_decode_desc* desc, const void* q, const void* k_cache,
   // units, so that a line meets few of them at a time.  Measured (contiguous and packed / items and
   // packed / items and spread, us): 23 requests of 3,895 positions at 38 shards, 2 KV heads of one query
   // head 22.2 / 25.6 / 21.7; 20 of 3,000 at 40, 4 KV heads 28.5 / 35.3 / 28.2; 32 of 32,768 at 64, 8 of two
-  // 688 / 718 / 690; 12 ragged ones of up to 7,003 at 16, 8 of two 34.6 / 27.2 / 27.5.
+  // 688 / 718 / 690; 12 ragged ones of up to 7,003 at 16, 8 of two 34.6 / 27.2 / 27.5.  With eight query heads a
+  // group's states are many, and its merge reads them from its own XCD's cache where they were written
+  // there: contiguous ranges too (8 requests of 5,549 at 26, 16 KV heads: items 100.2, ranges 89.5).
   const int32_t step = n_counters / qf::kCounterStep >= groups ? qf::kCounterStep : 1;
-  if (step == 1 && sp.p.run > 0) deal(&sp.p, (sp.p.n_units + 7) / 8);
+  if ((step == 1 || sp.group == 8) && sp.p.run > 0) deal(&sp.p, (sp.p.n_units + 7) / 8);
   const hipError_t e = qf::launch_decode_fused(sp.p, sp.group, counters, step, out, lse, s);
   if (e != hipSuccess) return fail(QF_EHIP, "decode launch: %s", hipGetErrorString(e));
   return QF_OK;
